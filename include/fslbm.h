@@ -268,8 +268,8 @@ void fslbm_batch_destroy(fslbm_batch_t b);
 /* Accumulated device time (ms) of the five phases of a step while
  * FSLBM_OPT_TIMING is on, phase_ms[5]: [0] stream-collide of liquid cells,
  * [1] stream-collide with mass exchange of interface cells, [2] cell
- * conversion, [3] interface-list compaction, [4] obstacle fill and
- * curvature; *steps receives the number of timed steps. Synchronises. */
+ * conversion and the update of the interface list, [3] nothing (the list
+ * update was a launch of its own), [4] obstacle fill and curvature; *steps receives the number of timed steps. Synchronises. */
 int fslbm_read_timing(fslbm_t h, double *phase_ms, int64_t *steps);
 int fslbm_reset_timing(fslbm_t h);
 

@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256) void k_snap(Fields<P> F, typename P::R *snap, 
     const size_t N = F.N;
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n + no; k += gridDim.x * 256) {
         if (k < n) {
-            const int i = F.ilist[k];
+            const int i = interface_list(F)[k];
             R *s = snap + (size_t)SNAP * k;
             if (save) {
                 s[0] = F.m[i]; s[1] = F.rho[i]; s[2] = F.phi[i]; s[3] = F.K[i];
@@ -106,7 +106,7 @@ __global__ void k_adj_begin(Fields<P> F, Adj A, const double *dphi)
 {
     const int n = F.sc->icount;
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
-        const int i = F.ilist[k];
+        const int i = interface_list(F)[k];
         A.pos[i] = k;
         A.phib[i] = dphi[i];
     }
@@ -138,7 +138,7 @@ __global__ void k_adj_finish(Fields<P> F, Adj A, const typename P::R *snap0, dou
 {
     const int n = F.sc->icount;
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
-        const int i = F.ilist[k];
+        const int i = interface_list(F)[k];
         out[i] = (A.phib[i] + reflected_phib(F, A, k, i)) + A.mbar[i] * double(snap0[(size_t)SNAP * k + 1]);
     }
 }
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256) void k_adj_prepass(Fields<P> F, Adj A, const t
     const size_t N = F.N;
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n + no; k += gridDim.x * 256) {
         if (k < n) {
-            const int i = F.ilist[k];
+            const int i = interface_list(F)[k];
             const double m = double(snap_next[(size_t)SNAP * k]), r = double(snap_next[(size_t)SNAP * k + 1]);
             const double pb = A.phib[i] + reflected_phib(F, A, k, i);
             A.mbar[i] += pb / r;
@@ -623,7 +623,7 @@ __global__ __launch_bounds__(256) void k_adj_reflect_setup(const Fields<P> F, co
     const int n = F.sc->icount;
     const double alpha = 0.70710678118654752440 + 1e-12;
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
-        const int i = F.ilist[k];
+        const int i = interface_list(F)[k];
         double *c = A.refl + (size_t)(NQ - 1) * k;
         const bool near = (F.flags[i] & FL_NEAR_OBST) != 0;
         const Nbr ni(i, F.nx, F.ny, F.nz);
@@ -1175,7 +1175,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     for (int k0 = blockIdx.x * per_block; k0 < n; k0 += cell_blocks * per_block) {
         const int k = k0 + cl;
         const bool on = k < n;
-        const int i = on ? F.ilist[k] : 0;
+        const int i = on ? interface_list(F)[k] : 0;
         const int yz = i / F.nx, x = i - yz * F.nx, z = yz / F.ny, y = yz - z * F.ny;
         double kb = 0.0;
         if (on) {
@@ -1210,7 +1210,7 @@ __device__ inline void plic_derivs_blocks(const Fields<P> &F, const Adj &A, int 
     const int n = F.sc->icount;
     const size_t N = F.N;
     for (int k = b * 256 + threadIdx.x; k < n; k += nb * 256) {
-        const int j = F.ilist[k];
+        const int j = interface_list(F)[k];
         const double nj[3] = {double(F.nrm[j]), double(F.nrm[N + j]), double(F.nrm[2 * N + j])};
         double dphi = 0.0, dn[3] = {0.0, 0.0, 0.0};
         if (nj[0] != 0.0 || nj[1] != 0.0 || nj[2] != 0.0) plic_derivs(nj, double(F.phi[j]), double(F.plic[j]), dphi, dn);
@@ -1235,7 +1235,7 @@ __global__ __launch_bounds__(256) void k_adj_lsqr_plic(const Fields<P> F, const 
     const int lane = threadIdx.x % ADJ_LANES;
     constexpr int per_block = 256 / ADJ_LANES;
     for (int k = blockIdx.x * per_block + threadIdx.x / ADJ_LANES; k < n; k += gridDim.x * per_block) {
-        const int j = F.ilist[k];
+        const int j = interface_list(F)[k];
         const Nbr nb(j, F.nx, F.ny, F.nz);
         double nbar[3] = {0, 0, 0}, abar = 0, g[3] = {0, 0, 0};
         for (int s = lane; s < 27; s += ADJ_LANES) {
@@ -1286,7 +1286,7 @@ __global__ __launch_bounds__(256) void k_adj_lsqr_phib(const Fields<P> F, const 
 {
     const int n = F.sc->icount, no = F.sc->ocount;
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n + no; k += gridDim.x * 256) {
-        const int i = k < n ? F.ilist[k] : F.olist[k - n];
+        const int i = k < n ? interface_list(F)[k] : F.olist[k - n];
         const Nbr nb(i, F.nx, F.ny, F.nz);
         const double v = py_div_t(A.gb, F.N, nb);
         if (k < n) A.phib[i] += v;

@@ -57,8 +57,7 @@ size_t fbytes(int prec)
 size_t rbytes(int prec) { return prec == P_F64 ? 8 : 4; }
 
 struct Layout {
-    size_t fA, fB, flags, conv, near, mark, m, rho, phi, K, nrm, plic, share, phis, nmol, cnrm, ilist, olist, wlist, newlist,
-        ilist_tmp,
+    size_t fA, fB, flags, conv, near, mark, m, rho, phi, K, nrm, plic, cnrm, ilist, olist, wlist, newlist, ilist_tmp, clist,
         staging,
         counts, part, sc, total;
 };
@@ -98,15 +97,13 @@ Layout make_layout(int nx, int ny, int nz, int prec)
     L.K = take(N * rb);
     L.nrm = take(3 * N * rb);
     L.plic = take(N * rb);
-    L.share = take(N * rb);
-    L.phis = take(N * rb);
-    L.nmol = take(3 * N * rb);
     L.cnrm = take(3 * N * rb);
     L.ilist = take(4 * N);
     L.olist = take(4 * N);
     L.wlist = take(4 * N);
     L.newlist = take(4 * N);
     L.ilist_tmp = take(4 * N);
+    L.clist = take(4 * N);
     L.staging = take(8 * N + 512);  // N doubles for read-outs; the ordered interface list (count + N ints)
     L.counts = take(4 * (size_t)CMP_GRID);  // one count per compaction block (fixed grid)
     L.part = take(8 * (DIAG_VALUES * MASS_BLOCKS + 8));  // mass, bubble volume and diagnostics partials
@@ -261,15 +258,13 @@ Fields<P> make_fields(const fslbm_lattice *h)
     F.K = (R *)at(L.K);
     F.nrm = (R *)at(L.nrm);
     F.plic = (R *)at(L.plic);
-    F.share = (R *)at(L.share);
-    F.phis = (R *)at(L.phis);
-    F.nmol = (R *)at(L.nmol);
     F.cnrm = (R *)at(L.cnrm);
     F.ilist = (int32_t *)at(L.ilist);
     F.olist = (int32_t *)at(L.olist);
     F.wlist = (int32_t *)at(L.wlist);
     F.newlist = (int32_t *)at(L.newlist);
     F.ilist_tmp = (int32_t *)at(L.ilist_tmp);
+    F.clist = (int32_t *)at(L.clist);
     F.counts = (int *)at(L.counts);
     F.part = (double *)at(L.part);
     F.sc = (DevScalars *)at(L.sc);
@@ -286,6 +281,10 @@ inline int cell_blocks(int N) { return (N + 255) / 256; }
 inline int list_blocks(int N) { return std::min(LIST_GRID, std::max(1, (N + 255) / 256)); }
 inline int cmp_blocks(int N) { return std::min(CMP_GRID, (N + CMP_CELLS - 1) / CMP_CELLS); }
 constexpr int GEOM_GRID = 1024;  // blocks per lattice of the tiled geometry kernels
+// least blocks of the two kernels that spread converting cells over
+// wavefronts (4 and 8 cells per block): a step converts up to a few hundred
+// cells of a small lattice too
+constexpr int CONV_GRID = 64;
 constexpr int SC_LIST_GRID = 1024;  // blocks per lattice of the interface / wall-list stream-collide
 
 // ------------------------------------------------------ init kernels
@@ -313,6 +312,8 @@ __global__ void k_init_scalars(DevScalars *sc)
     sc->fill_out = 0;
     sc->fill_out_step = 0xffffffffu;
     sc->conv_out_step = 0xffffffffu;
+    sc->lsel = 0;
+    sc->done = 0;
     for (int k = 0; k < 6; ++k) sc->bbox[k] = 0;
     sc->fbox[0] = sc->fbox[1] = sc->fbox[2] = 1 << 30;
     sc->fbox[3] = sc->fbox[4] = sc->fbox[5] = -1;
@@ -380,12 +381,9 @@ __global__ void k_init_fields(Fields<P> F, const double *fill, const uint8_t *ty
     F.rho[i] = rho;
     F.K[i] = 0;
     F.plic[i] = 0;
-    F.share[i] = 0;
-    F.phis[i] = 0;
     const size_t N = F.N;
     for (int c = 0; c < 3; ++c) {
         F.nrm[c * N + i] = 0;
-        F.nmol[c * N + i] = 0;
         F.cnrm[c * N + i] = 0;
     }
     F.mark[i] = 0;
@@ -901,7 +899,7 @@ int enqueue_step_kernels(fslbm_batch *b, const void *fsrc = nullptr, void *fdst 
     int boxb = 1;
     for (auto *h : b->hs) boxb = std::max(boxb, h->box_blocks);
     const dim3 cg(boxb, n), sg(std::min(SC_LIST_GRID, cell_blocks(maxN)), n),
-        lg(batch_list_blocks(b, 256), n);
+        lg(batch_list_blocks(b, 256), n), vg(std::max(CONV_GRID, batch_list_blocks(b, 256)), n);
     mark(b, 0);
     b->split_last = split_now<P>(b) ? 1 : 0;
     if (b->split_last) {
@@ -919,13 +917,10 @@ int enqueue_step_kernels(fslbm_batch *b, const void *fsrc = nullptr, void *fdst 
     bool frozen = true;
     for (auto *h : b->hs) frozen &= h->frozen != 0;
     mark(b, 2);
-    if (!frozen) k_conv_mark_init<P><<<lg, 256, 0, st>>>(A);
-    if (!frozen) k_conv_close<P><<<lg, 256, 0, st>>>(A);
-    if (!frozen) k_conv_share_keep<P><<<lg, 256, 0, st>>>(A);
+    if (!frozen) k_conv_mark<P><<<vg, 256, 0, st>>>(A);
+    if (!frozen) k_conv_close<P><<<vg, 256, 0, st>>>(A);
     k_conv_gather<P><<<lg, 256, 0, st>>>(A);
     mark(b, 3);
-    HIP_OK(hipGetLastError());
-    if (!frozen) k_list_finish<P><<<lg, 256, 0, st>>>(A);
     HIP_OK(hipGetLastError());
     int rc = 0;
     mark(b, 4);
@@ -1186,7 +1181,7 @@ __global__ void k_set_interface_fill(Fields<P> F, const double *fill)
     using R = typename P::R;
     const int n = F.sc->icount;
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
-        const int i = F.ilist[k];
+        const int i = interface_list(F)[k];
         const R phi = R(fill[i]);
         F.phi[i] = phi;
         F.m[i] = phi * F.rho[i];
@@ -1235,7 +1230,7 @@ std::vector<std::pair<size_t, size_t>> state_regions(const fslbm_lattice *h)
             {L.ilist, 4 * N},
             {L.olist, 4 * N},
             {L.wlist, 4 * N},
-            {L.sc, sizeof(DevScalars)}};
+            {L.sc, offsetof(DevScalars, lsel)}};
 }
 
 struct StateHeader {
@@ -1673,6 +1668,18 @@ int do_bubble_start(fslbm_lattice *h)
     return 0;
 }
 template <class P> struct OpBubble { static int run(fslbm_lattice *h) { return do_bubble_start<P>(h); } };
+
+// The interface list into the buffer that a saved state holds.
+template <class P>
+int do_list_home(fslbm_lattice *h)
+{
+    const Fields<P> F = make_fields<P>(h);
+    k_list_home<P><<<list_blocks(h->N), 256, 0, h->stream>>>(F);
+    k_list_reset<<<1, 1, 0, h->stream>>>(F.sc);
+    HIP_OK(hipGetLastError());
+    return 0;
+}
+template <class P> struct OpListHome { static int run(fslbm_lattice *h) { return do_list_home<P>(h); } };
 
 template <class P> struct OpFill { static int run(fslbm_lattice *h, const double *f, int d) { return do_set_interface_fill<P>(h, f, d); } };
 template <class P> struct OpAdjF { static int run(fslbm_lattice *h, long long T, int K, void *w, size_t b) { return do_adj_forward<P>(h, T, K, w, b); } };
@@ -2315,6 +2322,8 @@ int fslbm_save_state(fslbm_t h, void *dst, size_t bytes)
     if (!h) return fail(FSLBM_E_STATE, "null handle");
     if (!dst) return fail(FSLBM_E_ARG, "dst is NULL");
     if (bytes < state_bytes(h)) return fail(FSLBM_E_SHAPE, "state buffer has %zu bytes, %zu needed", bytes, state_bytes(h));
+    const int lrc = dispatch<OpListHome>(h);
+    if (lrc) return lrc;
     StateHeader hd{STATE_MAGIC, h->nx, h->ny, h->nz, h->prec, h->curv, 0, h->steps};
     char *d = (char *)dst;
     HIP_OK(hipMemcpyAsync(d, &hd, sizeof hd, hipMemcpyHostToDevice, h->stream));
@@ -2347,6 +2356,8 @@ int fslbm_load_state(fslbm_t h, const void *src, size_t bytes)
     h->steps = hd.steps;
     h->epoch += 1;
     h->version += 1;
+    k_list_reset<<<1, 1, 0, h->stream>>>((DevScalars *)(h->ws + h->L.sc));
+    HIP_OK(hipGetLastError());
     HIP_OK(hipStreamSynchronize(h->stream));
     // the loaded state brings its own obstacle list (launch sizing only)
     int ic = 0, oc = 0;

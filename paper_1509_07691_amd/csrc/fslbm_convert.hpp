@@ -22,11 +22,24 @@
 //   6  the cells take their new types.
 // Rule 4 starts from a closed layer (creation closes it), so only cells of
 // the step's layer (old interface cells and new cells) can break it.
-// Every kernel runs over the interface list of the step (grid-stride) and is
-// written as a gather: each output value has one writer, or several writers
-// storing the identical value (new cells reached from several converting
-// neighbours). New cells are tagged in `mark` with the step number, so no
-// clearing pass is needed. Kernels return at once when no cell converts.
+// Three launches per step, all of which return at once when no cell converts
+// (the last one then only sets phi = m / rho):
+//   k_conv_mark    one wavefront per filling or emptying cell (rules 2-3),
+//   k_conv_close   one thread per cell of the layer (rule 4) and one half
+//                  wavefront per new cell (the f' of rule 3),
+//   k_conv_gather  one thread per cell of the layer (rules 5-6), the new
+//                  interface list and its box.
+// The work is latency: a few hundred cells per step, each with two rings of
+// scattered neighbours. So the cells are spread over lanes (one lane per
+// neighbour), and a cell's neighbour types are loaded together rather than
+// one after the other. Each output value has one writer, or several writers
+// storing the identical value. New cells are tagged in `mark` with the step
+// number, so no clearing pass is needed. Measured per step, FP32: 41 us
+// (7 + 15 + 19) on a bubble carried through 97 x 61 x 83 at u = 0.05, 22 us
+// on the 256 x 256 x 128 sessile drop; with one thread per converting cell
+// (each computing the f' of up to 18 new cells from 342 neighbour loads in
+// turn), neighbours tested one by one and the list copied by a launch of its
+// own, the chain took five launches and 228 and 79 us there.
 #pragma once
 
 #include "fslbm_device.hpp"
@@ -38,49 +51,17 @@ constexpr int LIST_GRID = 256;  // blocks per lattice of the grid-stride list ke
 
 __device__ inline int list_count(const DevScalars *sc) { return *(volatile const int *)&sc->icount; }
 
-// A cell of the step's layer: an interface cell of the old list or a new
-// cell tagged in this step (its conv status is reset when it is tagged).
+// The interface list: the step that rebuilds it writes the other of the two
+// buffers, and its last block makes that one current.
 template <class P>
-__device__ inline bool in_layer(const Fields<P> &F, int j, uint32_t tag)
+__device__ inline const int32_t *interface_list(const Fields<P> &F)
 {
-    return (F.flags[j] & FL_IF) || (F.mark[j] & ~3u) == tag;
-}
-
-// A cell that leaves the layer in this step. From k_conv_share_keep on,
-// every such cell carries the step's tag: new cells from their tagging,
-// and old-list cells that convert get tag | 3 there. The test reads no
-// flags, so k_conv_gather can rewrite flags while it runs.
-template <class P>
-__device__ inline bool is_converter(const Fields<P> &F, int j, uint32_t tag)
-{
-    return (F.mark[j] & ~3u) == tag && F.conv[j] != CV_NONE;
+    return F.sc->lsel ? F.ilist_tmp : F.ilist;
 }
 
 // A new cell of this step (tagged 1 from gas or 2 from liquid; 3 marks an
 // old-list cell that leaves the layer).
 __device__ inline bool is_new(uint32_t mk, uint32_t tag) { return (mk & ~3u) == tag && (mk & 3u) != 3u; }
-
-// Rule 2 for cell i: an emptying cell next to a filling cell does not
-// empty. Returns the cell's status after it. Readers of other cells' status
-// only test for CV_FILL, which this never writes or clears.
-template <class P>
-__device__ inline uint8_t prune_own(const Fields<P> &F, int i)
-{
-    uint8_t st = F.conv[i];
-    if (st != CV_EMPTY) return st;
-    const Nbr nb(i, F.nx, F.ny, F.nz);
-    bool near_fill = false;
-#pragma unroll
-    for (int q = 1; q < NQ; ++q) {
-        const int j = nb.at(dir_x(q), dir_y(q), dir_z(q));
-        near_fill |= (F.flags[j] & FL_IF) && F.conv[j] == CV_FILL;
-    }
-    if (near_fill) {
-        F.conv[i] = CV_NONE;
-        st = CV_NONE;
-    }
-    return st;
-}
 
 __device__ inline int wrap_any(int v, int n)
 {
@@ -88,309 +69,294 @@ __device__ inline int wrap_any(int v, int n)
     return v < 0 ? v + n : v;
 }
 
-// Rules 2 and 3: prune the cell's own emptying (it reads only its
-// neighbours' filling, which pruning never changes), then tag the new
-// interface cells and initialise them. Cells reached from several
-// converting neighbours are written identically by each. A filling or
-// emptying cell also stamps the 7x7x7 box around it in `near` with the low
-// byte of the step number: the closure of rule 4 can only change a cell
-// within two cells of one (the layer was closed before the step), and
-// the excess of rule 5 moves one cell further. A stale stamp that happens
-// to match only makes a cell be checked.
+__device__ inline int wrap_one(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
+
+// Rules 2 and 3, one wavefront per cell that the stream-collide listed as
+// filling or emptying (clist, nconv entries). Lane q < 19 looks at the
+// neighbour in direction q: rule 2 drops an emptying cell next to a filling
+// one (it reads only its neighbours' filling, which dropping never changes),
+// rule 3 tags the new interface cells and lists them once. The wavefront
+// then stamps the 7x7x7 box around the cell in `near` with the low byte of
+// the step number: the closure of rule 4 can only change a cell within two
+// cells of a converting one (the layer was closed before the step), and the
+// excess of rule 5 moves one cell further. A stale stamp that happens to
+// match only makes a cell be checked. The fluid box grows by every new cell
+// (a new cell from gas is fluid whether it stays in the layer or closes to
+// liquid).
 template <class P>
-__global__ __launch_bounds__(256) void k_conv_mark_init(const Batch<P> B)
+__global__ __launch_bounds__(256) void k_conv_mark(const Batch<P> B)
 {
     const Fields<P> &F = B.f[blockIdx.y];
-    using T = typename P::T;
-    using R = typename P::R;
-    if (F.sc->nconv == 0) return;
+    const int nc = *(volatile const int *)&F.sc->nconv;
+    if (nc == 0) return;
     const uint32_t tag = F.sc->step << 2;
-    const int n = list_count(F.sc);
-    const int N = F.N;
-    const int n_round = (n + 255) / 256 * 256;  // whole wavefronts iterate together
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < n_round; k += gridDim.x * 256) {
-        int fresh[NQ];
-        int nfresh = 0;
-        const int i = k < n ? F.ilist[k] : 0;
-        const uint8_t st = k < n ? prune_own(F, i) : CV_NONE;
-        if (st != CV_NONE) {
-            const uint8_t s8 = uint8_t(tag >> 2);
-            const int yz = i / F.nx, x = i - yz * F.nx, z = yz / F.ny, y = yz - z * F.ny;
-            for (int dz = -3; dz <= 3; ++dz)
-                for (int dy = -3; dy <= 3; ++dy) {
-                    const int row = F.nx * (wrap_any(y + dy, F.ny) + F.ny * wrap_any(z + dz, F.nz));
-                    for (int dx = -3; dx <= 3; ++dx) F.near[row + wrap_any(x + dx, F.nx)] = s8;
-                }
-        }
+    const uint8_t s8 = uint8_t(tag >> 2);
+    const int lane = threadIdx.x & 63, waves = gridDim.x * 4;
+    const int q = lane < NQ ? lane : 0;  // lanes without a direction read the cell itself
+    for (int c = blockIdx.x * 4 + (threadIdx.x >> 6); c < nc; c += waves) {
+        const int i = F.clist[c];
         const Nbr nb(i, F.nx, F.ny, F.nz);
-        for (int q = 1; q < NQ && st != CV_NONE; ++q) {
-            const int j = nb.at(dir_x(q), dir_y(q), dir_z(q));
-            const uint8_t tj = F.flags[j] & FL_TYPE;
-            if (st == CV_FILL && tj == FL_GAS) {
-                // the first thread to tag j lists it as a new interface cell
-                if ((atomicExch(&F.mark[j], tag | 1u) & ~3u) != tag) fresh[nfresh++] = j;
-                F.conv[j] = CV_NONE;
-                // mean rho and u over the liquid / interface neighbours of j
-                const Nbr nj(j, F.nx, F.ny, F.nz);
-                T rs = 0, usx = 0, usy = 0, usz = 0;
-                int cnt = 0;
-                for (int p = 1; p < NQ; ++p) {
-                    const int w = nj.at(dir_x(p), dir_y(p), dir_z(p));
-                    if (!(F.flags[w] & FL_FLUID)) continue;
-                    T fw[NQ];
+        const int j = nb.at(dir_x(q), dir_y(q), dir_z(q));
+        const uint8_t st = F.conv[i], cj = F.conv[j], fj = F.flags[j];
+        if (st == CV_EMPTY && __any(q != 0 && (fj & FL_IF) && cj == CV_FILL)) {
+            if (lane == 0) F.conv[i] = CV_NONE;
+            continue;
+        }
+        const uint8_t tj = fj & FL_TYPE;
+        const bool hit = q != 0 && tj == (st == CV_FILL ? FL_GAS : FL_LIQ);
+        bool fresh = false;
+        if (hit) {
+            const uint32_t mk = tag | (st == CV_FILL ? 1u : 2u);
+            // the first wavefront to tag j lists it as a new interface cell
+            fresh = (atomicExch(&F.mark[j], mk) & ~3u) != tag;
+            F.conv[j] = CV_NONE;
+        }
+        const unsigned long long fm = __ballot(fresh);
+        if (fm) {
+            int base = 0;
+            if (lane == 0) base = atomicAdd(&F.sc->nnew, __popcll(fm));
+            base = __shfl(base, 0, 64);
+            if (fresh) {
+                F.newlist[base + __popcll(fm & ((1ull << lane) - 1ull))] = j;
+                const int yz = j / F.nx, z = yz / F.ny;
+                const int v[3] = {j - yz * F.nx, yz - z * F.ny, z};
 #pragma unroll
-                    for (int s = 0; s < NQ; ++s) {
-                        switch (s) {
-#define FSLBM_LD(QQ) case QQ: fw[s] = load_f<P, QQ>(plane<P, QQ>((const typename P::S *)F.fdst, F.NS), w); break;
-                            FSLBM_LD(0) FSLBM_LD(1) FSLBM_LD(2) FSLBM_LD(3) FSLBM_LD(4) FSLBM_LD(5)
-                            FSLBM_LD(6) FSLBM_LD(7) FSLBM_LD(8) FSLBM_LD(9) FSLBM_LD(10) FSLBM_LD(11)
-                            FSLBM_LD(12) FSLBM_LD(13) FSLBM_LD(14) FSLBM_LD(15) FSLBM_LD(16)
-                            FSLBM_LD(17) FSLBM_LD(18)
-#undef FSLBM_LD
-                        }
-                    }
-                    T r, ux, uy, uz;
-                    moments(fw, r, ux, uy, uz);
-                    rs += r; usx += ux; usy += uy; usz += uz;
-                    ++cnt;
+                for (int k = 0; k < 3; ++k) {
+                    if (v[k] < F.sc->fbox[k]) atomicMin(&F.sc->fbox[k], v[k]);
+                    if (v[k] > F.sc->fbox[3 + k]) atomicMax(&F.sc->fbox[3 + k], v[k]);
                 }
-                const T rm = rs / T(cnt), ux = usx / T(cnt), uy = usy / T(cnt), uz = usz / T(cnt);
-                const T usq = ux * ux + uy * uy + uz * uz;
-#pragma unroll
-                for (int s = 0; s < NQ; ++s) {
-                    const T v = feq<T>(s, rm, ux, uy, uz, usq);
-                    switch (s) {
-#define FSLBM_ST(QQ) case QQ: store_f<P, QQ>(plane<P, QQ>(F.fdst, F.NS), j, v); break;
-                        FSLBM_ST(0) FSLBM_ST(1) FSLBM_ST(2) FSLBM_ST(3) FSLBM_ST(4) FSLBM_ST(5)
-                        FSLBM_ST(6) FSLBM_ST(7) FSLBM_ST(8) FSLBM_ST(9) FSLBM_ST(10) FSLBM_ST(11)
-                        FSLBM_ST(12) FSLBM_ST(13) FSLBM_ST(14) FSLBM_ST(15) FSLBM_ST(16)
-                        FSLBM_ST(17) FSLBM_ST(18)
-#undef FSLBM_ST
-                    }
-                }
-                F.rho[j] = R(rm);
-                F.m[j] = R(0);
-            } else if (st == CV_EMPTY && tj == FL_LIQ) {
-                if ((atomicExch(&F.mark[j], tag | 2u) & ~3u) != tag) fresh[nfresh++] = j;
-                F.conv[j] = CV_NONE;
-                T fw[NQ];
-#pragma unroll
-                for (int s = 0; s < NQ; ++s) {
-                    switch (s) {
-#define FSLBM_LD(QQ) case QQ: fw[s] = load_f<P, QQ>(plane<P, QQ>((const typename P::S *)F.fdst, F.NS), j); break;
-                        FSLBM_LD(0) FSLBM_LD(1) FSLBM_LD(2) FSLBM_LD(3) FSLBM_LD(4) FSLBM_LD(5)
-                        FSLBM_LD(6) FSLBM_LD(7) FSLBM_LD(8) FSLBM_LD(9) FSLBM_LD(10) FSLBM_LD(11)
-                        FSLBM_LD(12) FSLBM_LD(13) FSLBM_LD(14) FSLBM_LD(15) FSLBM_LD(16)
-                        FSLBM_LD(17) FSLBM_LD(18)
-#undef FSLBM_LD
-                    }
-                }
-                T r = 0;
-#pragma unroll
-                for (int s = 0; s < NQ; ++s) r += fw[s];
-                F.rho[j] = R(r);
-                F.m[j] = R(r);
             }
         }
-        // one atomic per wavefront for the new cells found by its lanes
-        const int lane = threadIdx.x & 63;
-        int incl = nfresh;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
-            const int y = __shfl_up(incl, d, 64);
-            if (lane >= d) incl += y;
+        for (int t = lane; t < 343; t += 64) {  // one wrap covers an offset of 3 for extents >= 3
+            const int dx = t % 7 - 3, dy = (t / 7) % 7 - 3, dz = t / 49 - 3;
+            F.near[wrap_one(nb.x + dx, F.nx) + F.nx * (wrap_one(nb.y + dy, F.ny) + F.ny * wrap_one(nb.z + dz, F.nz))] = s8;
         }
-        const int total = __shfl(incl, 63, 64);
-        int base = 0;
-        if (lane == 63 && total > 0) base = atomicAdd(&F.sc->nnew, total);
-        base = __shfl(base, 63, 64) + incl - nfresh;
-        for (int s = 0; s < nfresh; ++s) F.newlist[base + s] = fresh[s];
     }
 }
 
-// Cell types after rules 1-3 (CLOSE_* codes read as interface): the
-// classification rule 4 starts from.
-template <class P>
-__device__ inline uint8_t type_after_conversion(const Fields<P> &F, int j, uint32_t tag)
+// Cell type after rules 1-3 (CLOSE_* codes read as interface) from a cell's
+// flags, mark and status: the classification rule 4 starts from. A cell that
+// is tagged as leaving in the same launch reads the same before and after.
+__device__ inline uint8_t type_after(uint8_t f, uint32_t mk, uint8_t st, uint32_t tag)
 {
-    const uint8_t f = F.flags[j];
-    if ((F.mark[j] & ~3u) == tag) return FL_IF;
+    if (is_new(mk, tag)) return FL_IF;
     if (!(f & FL_IF)) return f & FL_TYPE;
-    const uint8_t st = F.conv[j];
     return st == CV_FILL ? FL_LIQ : (st == CV_EMPTY ? FL_GAS : FL_IF);
+}
+
+// The types of cell c's neighbours in the directions 1..18, loaded together.
+template <class P>
+__device__ inline void neighbour_types(const Fields<P> &F, const Nbr &nb, uint32_t tag, uint8_t (&t)[NQ])
+{
+    uint8_t f[NQ], st[NQ];
+    uint32_t mk[NQ];
+#pragma unroll
+    for (int q = 1; q < NQ; ++q) {
+        const int j = nb.at(dir_x(q), dir_y(q), dir_z(q));
+        f[q] = F.flags[j];
+        mk[q] = F.mark[j];
+        st[q] = F.conv[j];
+    }
+#pragma unroll
+    for (int q = 1; q < NQ; ++q) t[q] = type_after(f[q], mk[q], st[q], tag);
 }
 
 // Cell k of the step's layer: the old list, then the new cells.
 template <class P>
-__device__ inline int layer_cell(const Fields<P> &F, int k, int n)
+__device__ inline int layer_cell(const Fields<P> &F, const int32_t *list, int k, int n)
 {
-    return k < n ? F.ilist[k] : F.newlist[k - n];
+    return k < n ? list[k] : F.newlist[k - n];
 }
 
-// Rule 4 for layer cell c (types after rules 1-3, CLOSE_* codes read as
-// interface): without a gas neighbour c becomes liquid; otherwise, without
-// a neighbour that is liquid after the first pass (liquid, or a layer cell
-// without a gas neighbour) c becomes gas.
+// f' of a new cell (rule 3), by the 32 lanes of a half wavefront. From gas:
+// feq(mean rho, mean u) of its liquid / interface neighbours (types before
+// the step), lane p holding the moments of neighbour p, added in direction
+// order; m = 0. From liquid: f' stays, rho is its sum in direction order and
+// m = rho.
 template <class P>
-__device__ inline bool lacks_gas_neighbour(const Fields<P> &F, int c, uint32_t tag)
+__device__ inline void init_new_cell(const Fields<P> &F, int j, int lane)
 {
-    const Nbr nb(c, F.nx, F.ny, F.nz);
-    bool found = false;
+    using T = typename P::T;
+    using R = typename P::R;
+    const typename P::S *f = F.fdst;
+    const int p = lane < NQ ? lane : 0;
+    if ((F.mark[j] & 3u) == 1u) {
+        const Nbr nj(j, F.nx, F.ny, F.nz);
+        const int w = nj.at(dir_x(p), dir_y(p), dir_z(p));
+        const int fluid = p != 0 && (F.flags[w] & FL_FLUID) ? 1 : 0;
+        T r = 0, ux = 0, uy = 0, uz = 0;
+        if (fluid) {
+            T fw[NQ];
 #pragma unroll
-    for (int q = 1; q < NQ; ++q) found |= type_after_conversion(F, nb.at(dir_x(q), dir_y(q), dir_z(q)), tag) == FL_GAS;
-    return !found;
+            for (int s = 0; s < NQ; ++s) {
+                switch (s) {
+#define FSLBM_LD(QQ) case QQ: fw[s] = load_f<P, QQ>(plane<P, QQ>(f, F.NS), w); break;
+                    FSLBM_LD(0) FSLBM_LD(1) FSLBM_LD(2) FSLBM_LD(3) FSLBM_LD(4) FSLBM_LD(5)
+                    FSLBM_LD(6) FSLBM_LD(7) FSLBM_LD(8) FSLBM_LD(9) FSLBM_LD(10) FSLBM_LD(11)
+                    FSLBM_LD(12) FSLBM_LD(13) FSLBM_LD(14) FSLBM_LD(15) FSLBM_LD(16)
+                    FSLBM_LD(17) FSLBM_LD(18)
+#undef FSLBM_LD
+                }
+            }
+            moments(fw, r, ux, uy, uz);
+        }
+        T rs = 0, usx = 0, usy = 0, usz = 0;
+        int cnt = 0;
+        for (int s = 1; s < NQ; ++s) {
+            const T a = __shfl(r, s, 32), bx = __shfl(ux, s, 32), by = __shfl(uy, s, 32), bz = __shfl(uz, s, 32);
+            if (!__shfl(fluid, s, 32)) continue;
+            rs += a; usx += bx; usy += by; usz += bz;
+            ++cnt;
+        }
+        const T rm = rs / T(cnt), vx = usx / T(cnt), vy = usy / T(cnt), vz = usz / T(cnt);
+        const T v = feq<T>(p, rm, vx, vy, vz, vx * vx + vy * vy + vz * vz);
+        typename P::S *dst = F.fdst + (size_t)p * (size_t)F.NS + j;
+        if (lane < NQ) {
+            if constexpr (P::SHIFT) store_rn(dst, (v - weight<T>(p)) * T(P::SCALE));
+            else __builtin_nontemporal_store(v, dst);
+        }
+        if (lane == 0) {
+            F.rho[j] = R(rm);
+            F.m[j] = R(0);
+        }
+    } else {
+        T v = 0;
+        if constexpr (P::SHIFT) v = weight<T>(p) + to_float(f[(size_t)p * (size_t)F.NS + j]) * T(1.0 / P::SCALE);
+        else v = f[(size_t)p * (size_t)F.NS + j];
+        T r = 0;
+        for (int s = 0; s < NQ; ++s) r += __shfl(v, s, 32);
+        if (lane == 0) {
+            F.rho[j] = R(r);
+            F.m[j] = R(r);
+        }
+    }
 }
 
-// Rule 4, both passes in one launch: each cell writes only its own status,
-// and a neighbour's first-pass result is evaluated, not read, so no thread
-// depends on another's write. The second pass looks two cells out only for
-// a cell without a liquid neighbour after rules 1-3, which is rare.
+// Rule 4, both passes in one launch: without a gas neighbour a cell becomes
+// liquid; otherwise, without a neighbour that is liquid after the first pass
+// (liquid, or a layer cell without a gas neighbour), it becomes gas. Each
+// cell writes only its own status, and a neighbour's first-pass result is
+// evaluated, not read, so no thread depends on another's write. The second
+// pass looks two cells out only for a cell without a liquid neighbour after
+// rules 1-3, which is rare. Every old-list cell that leaves the layer is
+// tagged tag | 3, which k_conv_gather tells it by. The new cells' f' (an
+// independent job) rides on the same launch.
 template <class P>
 __global__ __launch_bounds__(256) void k_conv_close(const Batch<P> B)
 {
     const Fields<P> &F = B.f[blockIdx.y];
     if (F.sc->nconv == 0) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {  // counters of the list rebuild in k_conv_share_keep
+    if (blockIdx.x == 0 && threadIdx.x == 0) {  // counters of the list rebuild in k_conv_gather
         F.sc->nkeep = 0;
+        F.sc->done = 0;
         F.sc->bbox[0] = F.nx; F.sc->bbox[1] = F.ny; F.sc->bbox[2] = F.nz;
         F.sc->bbox[3] = -1; F.sc->bbox[4] = -1; F.sc->bbox[5] = -1;
     }
     const uint32_t tag = F.sc->step << 2;
     const uint8_t s8 = uint8_t(tag >> 2);
     const int n = list_count(F.sc), nn = F.sc->nnew;
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < n + nn; k += gridDim.x * 256) {
-        const int i = layer_cell(F, k, n);
-        if (F.near[i] != s8 || F.conv[i] != CV_NONE) continue;
-        // most cells have both a gas and a liquid neighbour: stop at the
-        // first of each
-        const Nbr nb(i, F.nx, F.ny, F.nz);
-        bool gas = false, liquid = false;
-        for (int q = 1; q < NQ && !(gas && liquid); ++q) {
-            const uint8_t t = type_after_conversion(F, nb.at(dir_x(q), dir_y(q), dir_z(q)), tag);
-            gas |= t == FL_GAS;
-            liquid |= t == FL_LIQ;
+    const int32_t *list = interface_list(F);
+    for (int m = blockIdx.x * 8 + (int)(threadIdx.x >> 5); m < nn; m += gridDim.x * 8)
+        init_new_cell(F, F.newlist[m], threadIdx.x & 31);
+    const int lane = threadIdx.x & 63;
+    for (int k0 = blockIdx.x * 256; k0 < n + nn; k0 += gridDim.x * 256) {
+        const int k = k0 + (int)threadIdx.x;
+        const int i = k < n + nn ? layer_cell(F, list, k, n) : 0;
+        const bool on = k < n + nn && F.near[i] == s8;
+        const bool leaves = on && F.conv[i] != CV_NONE;
+        if (leaves && k < n) F.mark[i] = tag | 3u;
+        bool gas = true, liquid = true;
+        if (on && !leaves) {
+            uint8_t t[NQ];
+            neighbour_types(F, Nbr(i, F.nx, F.ny, F.nz), tag, t);
+            gas = liquid = false;
+#pragma unroll
+            for (int q = 1; q < NQ; ++q) {
+                gas |= t[q] == FL_GAS;
+                liquid |= t[q] == FL_LIQ;
+            }
         }
-        if (!gas) {
-            F.conv[i] = CV_CLOSE_LIQ;
-            continue;
+        // the second pass, by the whole wavefront for one cell after the
+        // other: lane q asks whether neighbour q lacks a gas neighbour
+        unsigned long long need = __ballot(gas && !liquid);
+        while (need) {
+            const int l = __ffsll(need) - 1;
+            need &= need - 1;
+            const Nbr nc(__shfl(i, l, 64), F.nx, F.ny, F.nz);
+            const int q = lane < NQ ? lane : 0;
+            const int j = nc.at(dir_x(q), dir_y(q), dir_z(q));
+            bool ok = false;
+            if (q != 0 && type_after(F.flags[j], F.mark[j], F.conv[j], tag) == FL_IF) {
+                uint8_t u[NQ];
+                neighbour_types(F, Nbr(j, F.nx, F.ny, F.nz), tag, u);
+                ok = true;
+#pragma unroll
+                for (int p = 1; p < NQ; ++p) ok &= u[p] != FL_GAS;
+            }
+            const bool found = __any(ok);
+            if (lane == l) liquid = found;
         }
-        for (int q = 1; q < NQ && !liquid; ++q) {
-            const int j = nb.at(dir_x(q), dir_y(q), dir_z(q));
-            liquid = type_after_conversion(F, j, tag) == FL_IF && lacks_gas_neighbour(F, j, tag);
-        }
-        if (!liquid) F.conv[i] = CV_CLOSE_GAS;
+        if (gas && liquid) continue;
+        F.conv[i] = gas ? CV_CLOSE_GAS : CV_CLOSE_LIQ;
+        if (k < n) F.mark[i] = tag | 3u;
     }
 }
 
+// Rule 5 for a cell w that leaves the layer: its excess, and the number of
+// its neighbours that receive (cells of the layer that stay; every converter
+// has a status, so the types that k_conv_gather rewrites do not enter).
 template <class P>
-__device__ inline bool is_receiver(const Fields<P> &F, int j, uint32_t tag)
+__device__ inline int receivers(const Fields<P> &F, const Nbr &nw, uint32_t tag)
 {
-    return in_layer(F, j, tag) && F.conv[j] == CV_NONE;
-}
-
-// Rule 5, first half: a cell that leaves the layer computes its share
-// (run by k_conv_share_keep); an old-list cell is tagged tag | 3 (its own
-// thread writes it; the neighbours' receiver test reads flags or the tag,
-// both of which mark it as a layer cell).
-template <class P>
-__device__ inline void conv_share_cell(const Fields<P> &F, int i, uint32_t tag, bool old_list)
-{
-    using R = typename P::R;
-    const uint8_t st = F.conv[i];
-    if (st == CV_NONE) return;
-    if (old_list) F.mark[i] = tag | 3u;
-    const R mex = cv_to_liquid(st) ? F.m[i] - F.rho[i] : F.m[i];
-    const Nbr nb(i, F.nx, F.ny, F.nz);
+    uint8_t f[NQ], st[NQ];
+    uint32_t mk[NQ];
+#pragma unroll
+    for (int q = 1; q < NQ; ++q) {
+        const int j = nw.at(dir_x(q), dir_y(q), dir_z(q));
+        f[q] = F.flags[j];
+        mk[q] = F.mark[j];
+        st[q] = F.conv[j];
+    }
     int cnt = 0;
 #pragma unroll
-    for (int q = 1; q < NQ; ++q) cnt += is_receiver(F, nb.at(dir_x(q), dir_y(q), dir_z(q)), tag);
-    if (cnt > 0) {
-        F.share[i] = mex / R(cnt);
-    } else {
-        F.share[i] = R(0);
-        reservoir_add(F.sc, (double)mex);
-    }
+    for (int q = 1; q < NQ; ++q) cnt += ((f[q] & FL_IF) || (mk[q] & ~3u) == tag) && st[q] == CV_NONE;
+    return cnt;
+}
+template <class P>
+__device__ inline typename P::R excess_mass(const Fields<P> &F, int w)
+{
+    return cv_to_liquid(F.conv[w]) ? F.m[w] - F.rho[w] : F.m[w];
 }
 
+// The shares that reach cell j, in direction order: the neighbours that
+// leave are collected first, then evaluated one after the other (one or two
+// per receiving cell, so the lanes of a wavefront share the few rounds).
 template <class P>
 __device__ inline typename P::R gathered_excess(const Fields<P> &F, int j, uint32_t tag)
 {
     using R = typename P::R;
     const Nbr nb(j, F.nx, F.ny, F.nz);
-    R acc = 0;
+    uint32_t mk[NQ], from = 0;
+    uint8_t st[NQ];
 #pragma unroll
     for (int q = 1; q < NQ; ++q) {
         const int w = nb.at(dir_x(q), dir_y(q), dir_z(q));
-        if (is_converter(F, w, tag)) acc += F.share[w];
+        mk[q] = F.mark[w];
+        st[q] = F.conv[w];
+    }
+#pragma unroll
+    for (int q = 1; q < NQ; ++q) from |= (mk[q] & ~3u) == tag && st[q] != CV_NONE ? 1u << q : 0u;
+    R acc = 0;
+    while (from) {
+        const int q = __ffs(from) - 1;
+        from &= from - 1;
+        const int w = nb.at(dir_x(q), dir_y(q), dir_z(q));
+        const Nbr nw(w, F.nx, F.ny, F.nz);
+        acc += excess_mass(F, w) / R(receivers(F, nw, tag));
     }
     return acc;
 }
 
-// Rule 5, second half, and rule 6: receivers gather their neighbours'
-// shares in fixed direction order, and the cells that leave the layer and
-// the new cells take their types. This kernel also sets phi = m / rho of
-// every interface cell for the new time level, so it runs in every step.
-// Every new cell is next to a filling or emptying cell of the old list,
-// whose thread sets it (several threads may write the same values).
-template <class P>
-__global__ __launch_bounds__(256) void k_conv_gather(const Batch<P> B)
-{
-    const Fields<P> &F = B.f[blockIdx.y];
-    const bool frozen = B.p[blockIdx.y].frozen != 0;
-    using R = typename P::R;
-    const bool any = F.sc->nconv != 0;
-    const uint32_t tag = F.sc->step << 2;
-    const uint8_t s8 = uint8_t(tag >> 2);
-    const int n = list_count(F.sc);
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
-        const int i = F.ilist[k];
-        const uint8_t st = any ? F.conv[i] : CV_NONE;
-        if (st == CV_NONE) {
-            // only a cell near a filling or emptying cell can receive
-            const R acc = any && F.near[i] == s8 ? gathered_excess(F, i, tag) : R(0);
-            const R mn = F.m[i] + acc;
-            const R ph = mn / F.rho[i];
-            F.m[i] = mn;
-            F.phi[i] = ph;
-            // a frozen window stays on one smooth piece of the step only while
-            // every interface fill lies strictly inside (0, 1)
-            if (frozen && !(ph > R(0) && ph < R(1))) {
-                atomicAdd(&F.sc->fill_out, 1);
-                atomicMin(&F.sc->fill_out_step, F.sc->step);
-            }
-            continue;
-        }
-        F.phi[i] = cv_to_liquid(st) ? R(1) : R(0);
-        F.flags[i] = (F.flags[i] & FL_NEAR_OBST) | (cv_to_liquid(st) ? FL_LIQ : FL_GAS);
-        // a new neighbour of a closing cell is also next to the filling or
-        // emptying cell that made it, whose thread sets it
-        if (st == CV_CLOSE_LIQ || st == CV_CLOSE_GAS) continue;
-        const Nbr nb(i, F.nx, F.ny, F.nz);
-        for (int q = 1; q < NQ; ++q) {
-            const int j = nb.at(dir_x(q), dir_y(q), dir_z(q));
-            const uint32_t mk = F.mark[j];
-            if (!is_new(mk, tag)) continue;
-            const uint8_t sj = F.conv[j];
-            const uint8_t tj = sj == CV_NONE ? FL_IF : (cv_to_liquid(sj) ? FL_LIQ : FL_GAS);
-            F.flags[j] = (F.flags[j] & FL_NEAR_OBST) | tj;
-            if (sj != CV_NONE) {
-                F.phi[j] = cv_to_liquid(sj) ? R(1) : R(0);
-                continue;
-            }
-            const R base = (mk & 3u) == 1u ? R(0) : F.rho[j];
-            const R mn = base + gathered_excess(F, j, tag);
-            F.m[j] = mn;
-            F.phi[j] = mn / F.rho[j];
-        }
-    }
-}
-
-// ------------------------------------------------ interface-list update
-// After a step with conversions the list becomes the cells of the step's
-// layer (old list, then new cells) that are interface cells. The order of
-// the list does not enter any result (every per-cell computation is
-// independent), so kept cells are appended with an atomic counter; the
-// interface bounding box is recomputed on the way.
 __device__ inline int block_exclusive_scan(int v, int *lds_wave, int &total)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -454,62 +420,97 @@ __device__ inline void box_add(const Fields<P> &F, int i, int (&lo)[3], int (&hi
     hi[0] = max(hi[0], x); hi[1] = max(hi[1], y); hi[2] = max(hi[2], z);
 }
 
-// Shares of the cells that leave the layer (rule 5, first half), and the
-// cells of the step's layer that stay interface cells (status CV_NONE after
-// rule 4, old or new), written in layer order within each block: a counting
-// pass, one atomic for the block's base, then the ordered write with a
-// block prefix sum. Each block takes one contiguous range of the layer.
+// Rules 5 and 6, one thread per cell of the layer (the old list, then the
+// new cells): receivers add their neighbours' shares, cells that leave take
+// their type (their excess goes to the reservoir when nobody receives it),
+// and the cells that stay are appended to the other list buffer, in order
+// within each 256-cell chunk; the last block to finish makes that buffer
+// current. The order of the list does not enter any result (every per-cell
+// computation is independent). Also sets phi = m / rho of every interface
+// cell for the new time level, so it runs in every step; without conversions
+// that is all it does.
 template <class P>
-__global__ __launch_bounds__(256) void k_conv_share_keep(const Batch<P> B)
+__global__ __launch_bounds__(256) void k_conv_gather(const Batch<P> B)
 {
     const Fields<P> &F = B.f[blockIdx.y];
-    if (F.sc->nconv == 0) return;
-    const uint32_t tag = F.sc->step << 2;
-    const int n = list_count(F.sc), nl = n + F.sc->nnew;
-    int k0, k1;
-    block_share(nl, k0, k1);
-    for (int k = k0 + threadIdx.x; k < k1; k += 256) conv_share_cell(F, layer_cell(F, k, n), tag, k < n);
+    using R = typename P::R;
+    const int n = list_count(F.sc);
+    const int32_t *list = interface_list(F);
+    if (F.sc->nconv == 0) {
+        const bool frozen = B.p[blockIdx.y].frozen != 0;
+        for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
+            const int i = list[k];
+            const R ph = F.m[i] / F.rho[i];
+            F.phi[i] = ph;
+            // a frozen window stays on one smooth piece of the step only while
+            // every interface fill lies strictly inside (0, 1)
+            if (frozen && !(ph > R(0) && ph < R(1))) {
+                atomicAdd(&F.sc->fill_out, 1);
+                atomicMin(&F.sc->fill_out_step, F.sc->step);
+            }
+        }
+        return;
+    }
     __shared__ int lw[4];
     __shared__ int base_s;
-    int cnt = 0;
-    for (int k = k0 + threadIdx.x; k < k1; k += 256) cnt += F.conv[layer_cell(F, k, n)] == CV_NONE;
-    int total;
-    block_exclusive_scan(cnt, lw, total);
-    if (threadIdx.x == 0) base_s = total > 0 ? atomicAdd(&F.sc->nkeep, total) : 0;
-    __syncthreads();
-    int pos = base_s;
+    const uint32_t tag = F.sc->step << 2;
+    const uint8_t s8 = uint8_t(tag >> 2);
+    const int nl = n + F.sc->nnew;
+    int32_t *out = F.sc->lsel ? F.ilist : F.ilist_tmp;
     int lo[3] = {1 << 30, 1 << 30, 1 << 30}, hi[3] = {-1, -1, -1};
-    for (int kk = k0; kk < k1; kk += 256) {
-        const int k = kk + threadIdx.x;
-        const int i = k < k1 ? layer_cell(F, k, n) : 0;
-        const bool keep = k < k1 && F.conv[i] == CV_NONE;
+    for (int k0 = blockIdx.x * 256; k0 < nl; k0 += gridDim.x * 256) {
+        const int k = k0 + (int)threadIdx.x;
+        bool keep = false;
+        int i = 0;
+        if (k < nl) {
+            i = layer_cell(F, list, k, n);
+            const uint8_t st = F.conv[i];
+            keep = st == CV_NONE;
+            if (keep) {
+                // only a cell near a filling or emptying cell can receive
+                const R mn = F.m[i] + (F.near[i] == s8 ? gathered_excess(F, i, tag) : R(0));
+                F.m[i] = mn;
+                F.phi[i] = mn / F.rho[i];
+                if (k >= n) F.flags[i] = (F.flags[i] & FL_NEAR_OBST) | FL_IF;
+            } else {
+                const Nbr nb(i, F.nx, F.ny, F.nz);
+                if (receivers(F, nb, tag) == 0) reservoir_add(F.sc, (double)excess_mass(F, i));
+                F.phi[i] = cv_to_liquid(st) ? R(1) : R(0);
+                F.flags[i] = (F.flags[i] & FL_NEAR_OBST) | (cv_to_liquid(st) ? FL_LIQ : FL_GAS);
+            }
+        }
         int tot;
         const int ex = block_exclusive_scan(keep ? 1 : 0, lw, tot);
+        if (threadIdx.x == 0) base_s = tot > 0 ? atomicAdd(&F.sc->nkeep, tot) : 0;
+        __syncthreads();
         if (keep) {
-            F.ilist_tmp[pos + ex] = i;
+            out[base_s + ex] = i;
             box_add(F, i, lo, hi);
         }
-        pos += tot;
     }
     block_box_update(lo, hi, F.sc->bbox);
+    if (threadIdx.x == 0) {
+        __threadfence();
+        if (atomicAdd(&F.sc->done, 1) == (int)gridDim.x - 1) {
+            F.sc->icount = atomicAdd(&F.sc->nkeep, 0);
+            F.sc->lsel ^= 1;
+        }
+    }
 }
 
-// New list = the kept cells. The fluid box grows by every new cell (a new
-// cell from gas is fluid whether it stays in the layer or closes to
-// liquid); the interface box came from k_conv_share_keep.
+// The current list back into ilist (state copies hold that buffer alone):
+// the entries, then the selector.
 template <class P>
-__global__ __launch_bounds__(256) void k_list_finish(const Batch<P> B)
+__global__ __launch_bounds__(256) void k_list_home(Fields<P> F)
 {
-    const Fields<P> &F = B.f[blockIdx.y];
-    if (F.sc->nconv == 0) return;
-    const int nk = F.sc->nkeep, nn = F.sc->nnew;
-    int lo[3] = {1 << 30, 1 << 30, 1 << 30}, hi[3] = {-1, -1, -1};
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < nk + nn; k += gridDim.x * 256) {
-        if (k < nk) F.ilist[k] = F.ilist_tmp[k];
-        else box_add(F, F.newlist[k - nk], lo, hi);
-    }
-    block_box_update(lo, hi, F.sc->fbox);
-    if (blockIdx.x == 0 && threadIdx.x == 0) F.sc->icount = nk;
+    if (!F.sc->lsel) return;
+    const int n = list_count(F.sc);
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) F.ilist[k] = F.ilist_tmp[k];
+}
+__global__ void k_list_reset(DevScalars *sc)
+{
+    sc->lsel = 0;
+    sc->done = 0;
 }
 
 // ----------------------------------------------------------- compaction

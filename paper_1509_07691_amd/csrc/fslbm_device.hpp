@@ -235,7 +235,7 @@ __device__ inline void store_d(typename P::S *__restrict__ plane, int i, typenam
 
 // ------------------------------------------------------ per-step scalars
 struct DevScalars {
-    int icount;         // number of interface cells in ilist
+    int icount;         // number of interface cells in the interface list
     int ocount;         // number of obstacle cells in olist (static)
     int nconv;          // interface cells that fill or empty in this step
     int nnew;           // new interface cells of this step (in newlist)
@@ -257,6 +257,9 @@ struct DevScalars {
     int fill_out;       // frozen window: (step, interface cell) events with a fill outside (0, 1)
     unsigned fill_out_step;  // frozen window: step number of the first such event (UINT_MAX: none)
     unsigned conv_out_step;  // frozen window: step number of the first would-be fill or empty (UINT_MAX: none)
+    // not part of a saved state (a saved list is always in ilist)
+    int lsel;           // 1: the interface list is in ilist_tmp, 0: in ilist
+    int done;           // blocks of k_conv_gather that have finished
 };
 
 // A box of cells [x0, x0+ex) x [y0, y0+ey) x [z0, z0+ez) enumerated with x
@@ -313,16 +316,6 @@ __host__ inline int xcd_grid(long long chunks)
 {
     const long long g = (chunks + XCD_GRID - 1) / XCD_GRID * XCD_GRID;
     return (int)std::max<long long>(XCD_GRID, g);
-}
-
-// Contiguous share [k0, k1) of n items for block blockIdx.x of gridDim.x,
-// in whole 256-item strides.
-__device__ inline void block_share(int n, int &k0, int &k1)
-{
-    const int strides = (n + 255) / 256;
-    const int per = (strides + gridDim.x - 1) / gridDim.x;
-    k0 = min(n, (int)blockIdx.x * per * 256);
-    k1 = min(n, k0 + per * 256);
 }
 
 // Adds x to the fixed-point reservoir. |x| = a + b 2^-64 with a = floor|x|
@@ -395,11 +388,12 @@ template <class P> struct Fields {
     uint8_t *conv;
     uint8_t *near;  // low byte of the step number when within 2 cells of a filling or emptying cell
     uint32_t *mark;
-    R *m, *rho, *phi, *K, *nrm, *plic, *share, *phis, *nmol;
+    R *m, *rho, *phi, *K, *nrm, *plic;
     R *cnrm;           // FD wetting: contact normal of obstacle cells (3 planes, 0 = none)
-    int32_t *ilist, *olist;
+    int32_t *ilist, *olist;  // read the interface list through interface_list()
     int32_t *wlist;    // static: non-obstacle cells with an obstacle D3Q19 neighbour
-    int32_t *newlist, *ilist_tmp;  // new interface cells; scratch for the list rebuild
+    int32_t *newlist, *ilist_tmp;  // new interface cells; the interface list's other buffer
+    int32_t *clist;    // cells that fill or empty in this step (nconv entries)
     int *counts;       // per-block counts of the list compaction
     double *part;      // per-block partial sums of reductions
     DevScalars *sc;

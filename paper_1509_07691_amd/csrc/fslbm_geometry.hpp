@@ -909,7 +909,7 @@ __device__ inline void normals_plic_list(const Fields<P> &F)
     using G = typename P::G;
     const int n = list_count(F.sc);
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
-        const int i = F.ilist[k];
+        const int i = interface_list(F)[k];
         const Nbr nb(i, F.nx, F.ny, F.nz);
         G gx = 0, gy = 0, gz = 0;
 #pragma unroll
@@ -957,7 +957,7 @@ __global__ __launch_bounds__(256) void k_curv_lsqr(const Batch<P> B)
     using R = typename P::R;
     const int n = list_count(F.sc);
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
-        const int i = F.ilist[k];
+        const int i = interface_list(F)[k];
         const int yz = i / F.nx, x = i - yz * F.nx, z = yz / F.ny, y = yz - z * F.ny;
         const LsqrView<P> V{F, x, y, z};
         F.K[i] = R(lsqr_curvature(V, prm));
@@ -981,7 +981,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
     const int n = list_count(F.sc);
     const int l = threadIdx.x & 3;
     for (int k = blockIdx.x * 64 + (threadIdx.x >> 2); k < n; k += gridDim.x * 64) {
-        const int i = F.ilist[k];
+        const int i = interface_list(F)[k];
         const int yz = i / F.nx, x = i - yz * F.nx, z = yz / F.ny, y = yz - z * F.ny;
         const LsqrView<P> V{F, x, y, z};
         LsqrFrame f;
@@ -1067,7 +1067,7 @@ __global__ __launch_bounds__(256) void k_curv_tr(const Batch<P> B)
     const int n_round = (n + groups - 1) / groups * groups;  // whole groups iterate together
     for (int k = blockIdx.x * groups + (int)(threadIdx.x / TR_LANES); k < n_round; k += gridDim.x * groups) {
         const bool live = k < n;
-        const int i = live ? F.ilist[k] : 0;
+        const int i = live ? interface_list(F)[k] : 0;
         const int yz = i / F.nx, x = i - yz * F.nx, z = yz / F.ny, y = yz - z * F.ny;
         const LsqrView<P> V{F, x, y, z};
         LsqrFrame f;

@@ -10,7 +10,7 @@
 //   - eq. advection1/2 in mass form at interface cells (the incoming
 //     distribution f'_qbar(x + c_q) is exactly the pulled value),
 //   - moments and the SRT or TRT collision (eq. lbe2),
-//   - fill / empty classification of interface cells (counted only when
+//   - fill / empty classification of interface cells (listed only when
 //     cell types are not frozen, so that no conversion follows; a frozen
 //     window records the first step in which a cell would have converted).
 #pragma once
@@ -437,7 +437,7 @@ __device__ inline void boundary_cell(const Fields<P> &F, const Params &prm, int 
         F.rho[i] = R(r);
         F.conv[i] = st;
         if (st != CV_NONE) {
-            if (!prm.frozen) atomicAdd(&F.sc->nconv, 1);
+            if (!prm.frozen) F.clist[atomicAdd(&F.sc->nconv, 1)] = i;
             else atomicMin(&F.sc->conv_out_step, F.sc->step);  // the free method would convert here
         }
     }
@@ -531,7 +531,7 @@ __device__ inline void fluid_cell(const Fields<P> &F, const Params &prm, int i, 
             F.rho[i] = R(r);
             F.conv[i] = st;
             if (st != CV_NONE) {
-                if (!prm.frozen) atomicAdd(&F.sc->nconv, 1);
+                if (!prm.frozen) F.clist[atomicAdd(&F.sc->nconv, 1)] = i;
                 else atomicMin(&F.sc->conv_out_step, F.sc->step);  // the free method would convert here
             }
         }
@@ -615,8 +615,9 @@ __global__ __launch_bounds__(256) void k_stream_collide_list(const Batch<P> B)
     const Fields<P> &F = B.f[blockIdx.y];
     const int ni = *(volatile const int *)&F.sc->icount;
     const int n = ni + F.sc->wcount;
+    const int32_t *list = F.sc->lsel ? F.ilist_tmp : F.ilist;
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
-        const int i = k < ni ? F.ilist[k] : F.wlist[k - ni];
+        const int i = k < ni ? list[k] : F.wlist[k - ni];
         const Nbr nb(i, F.nx, F.ny, F.nz);
         if (k < ni) boundary_cell<P, COLL, true>(F, prm, i, nb);
         else if ((F.flags[i] & FL_TYPE) == FL_LIQ) boundary_cell<P, COLL, false>(F, prm, i, nb);
