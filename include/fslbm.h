@@ -201,12 +201,12 @@ int fslbm_read_flags(fslbm_t h, uint8_t *out, int out_is_device);
  * and liquid) as ascending linear indices into host out[capacity], found by
  * an ordered compaction of the cell types on the device; *count receives
  * their number (FSLBM_E_SHAPE if it exceeds capacity; out may be NULL to
- * query the count). Uses scratch inside the lattice's workspace and
+ * query the count, which the device keeps). Uses scratch inside the lattice's workspace and
  * synchronises the stream. FSLBM_E_ARG if count is NULL. */
 int fslbm_read_interface_list(fslbm_t h, int32_t *out, int64_t capacity, int64_t *count);
 /* The same read-out for callers that cannot allocate device memory (code
  * under graph capture, serving loops, harnesses that forbid hipMalloc): the
- * compaction's scratch (block counts, total and the staged list) lives in a
+ * compaction's scratch (block counts and the staged list) lives in a
  * file-scope device array of 16 MiB that each device holds until the
  * process ends, so this call allocates nothing. It holds at most 4,193,792
  * interface cells: a longer list is rejected with FSLBM_E_SHAPE (nothing is
@@ -269,7 +269,8 @@ void fslbm_batch_destroy(fslbm_batch_t b);
  * FSLBM_OPT_TIMING is on, phase_ms[5]: [0] stream-collide of liquid cells,
  * [1] stream-collide with mass exchange of interface cells, [2] cell
  * conversion and the update of the interface list, [3] nothing (the list
- * update was a launch of its own), [4] obstacle fill and curvature; *steps receives the number of timed steps. Synchronises. */
+ * update was a launch of its own), [4] obstacle fill and curvature; *steps
+ * receives the number of timed steps. Synchronises. */
 int fslbm_read_timing(fslbm_t h, double *phase_ms, int64_t *steps);
 int fslbm_reset_timing(fslbm_t h);
 

@@ -104,7 +104,7 @@ Layout make_layout(int nx, int ny, int nz, int prec)
     L.newlist = take(4 * N);
     L.ilist_tmp = take(4 * N);
     L.clist = take(4 * N);
-    L.staging = take(8 * N + 512);  // N doubles for read-outs; the ordered interface list (count + N ints)
+    L.staging = take(8 * N + 512);  // N doubles for read-outs; the ordered interface list (N ints)
     L.counts = take(4 * (size_t)CMP_GRID);  // one count per compaction block (fixed grid)
     L.part = take(8 * (DIAG_VALUES * MASS_BLOCKS + 8));  // mass, bubble volume and diagnostics partials
     L.sc = take(sizeof(DevScalars));
@@ -521,115 +521,190 @@ __device__ inline void cell_moments(const Fields<P> &F, int i, double &rho, type
 
 enum ReadWhat { RD_FILL, RD_PRESSURE, RD_CURV, RD_VEL, RD_NORMAL, RD_PLIC, RD_MASS };
 
-template <class P>
-__global__ void k_read(Fields<P> F, double rho_gas, int bubble, int what, int comp, double *out)
+// One field, or the three components of one (component-major), as doubles.
+// Bound by memory: the moments read the 19 planes once for all components
+// (a launch per component took 2.0 ms each on the 512^3 FP32 box), and the
+// scalar fields, 13 bytes per cell, move READ_CELLS cells per thread, a
+// block's cells 256 apart so that any alignment of `out` is coalesced.
+constexpr int READ_CELLS = 4;
+template <class P, int WHAT>
+__global__ __launch_bounds__(256) void k_read(Fields<P> F, double rho_gas, int bubble, double *out)
 {
-    using T = typename P::T;
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= F.N) return;
-    const uint8_t fl = F.flags[i];
-    const bool fluid = fl & FL_FLUID, ifc = fl & FL_IF;
     const size_t N = F.N;
-    double v = 0.0;
-    switch (what) {
-    case RD_FILL: v = double(F.phi[i]); break;
-    case RD_CURV: v = ifc ? double(F.K[i]) : 0.0; break;
-    case RD_NORMAL: v = ifc ? double(F.nrm[comp * N + i]) : 0.0; break;
-    case RD_PLIC: v = ifc ? double(F.plic[i]) : 0.0; break;
-    case RD_MASS: v = ifc ? double(F.m[i]) : 0.0; break;
-    case RD_PRESSURE:
-    case RD_VEL:
-        if (fluid) {
-            double r;
-            T ux, uy, uz;
-            cell_moments(F, i, r, ux, uy, uz);
-            if (what == RD_PRESSURE) v = r / 3.0;
-            else v = double(comp == 0 ? ux : (comp == 1 ? uy : uz));
-        } else if (what == RD_PRESSURE) {
-            v = (fl & FL_GAS) ? (bubble ? F.sc->rho_gas_t : rho_gas) / 3.0 : 0.0;
+    if constexpr (WHAT == RD_PRESSURE || WHAT == RD_VEL) {
+        using T = typename P::T;
+        const int i = blockIdx.x * 256 + threadIdx.x;
+        if (i >= F.N) return;
+        const uint8_t fl = F.flags[i];
+        double r = 0.0;
+        T ux = 0, uy = 0, uz = 0;
+        if (fl & FL_FLUID) cell_moments(F, i, r, ux, uy, uz);
+        if constexpr (WHAT == RD_VEL) {
+            __builtin_nontemporal_store(double(ux), out + i);
+            __builtin_nontemporal_store(double(uy), out + N + i);
+            __builtin_nontemporal_store(double(uz), out + 2 * N + i);
+        } else {
+            double v = r / 3.0;
+            if (!(fl & FL_FLUID)) v = (fl & FL_GAS) ? (bubble ? F.sc->rho_gas_t : rho_gas) / 3.0 : 0.0;
+            __builtin_nontemporal_store(v, out + i);
         }
-        break;
+    } else {
+        using R = typename P::R;
+        constexpr int COMPS = WHAT == RD_NORMAL ? 3 : 1;
+        const R *f = WHAT == RD_FILL ? F.phi : (WHAT == RD_CURV ? F.K : (WHAT == RD_NORMAL ? F.nrm : (WHAT == RD_PLIC ? F.plic : F.m)));
+        const long long i0 = (long long)blockIdx.x * (256 * READ_CELLS) + threadIdx.x;
+        R v[COMPS][READ_CELLS];
+        uint8_t fl[READ_CELLS];
+#pragma unroll
+        for (int s = 0; s < READ_CELLS; ++s) {
+            const long long i = i0 + 256 * s;
+            if (i >= F.N) continue;
+            if (WHAT != RD_FILL) fl[s] = F.flags[i];
+#pragma unroll
+            for (int c = 0; c < COMPS; ++c) v[c][s] = f[c * N + i];
+        }
+#pragma unroll
+        for (int s = 0; s < READ_CELLS; ++s) {
+            const long long i = i0 + 256 * s;
+            if (i >= F.N) continue;
+            const bool on = WHAT == RD_FILL || (fl[s] & FL_IF);
+#pragma unroll
+            for (int c = 0; c < COMPS; ++c) __builtin_nontemporal_store(on ? double(v[c][s]) : 0.0, out + c * N + i);
+        }
     }
-    out[i] = v;
 }
 
-// Ascending list of the interface cells (read-out): CMP_GRID blocks, each
-// owning a contiguous run of 1024-cell tiles of the fluid box; per-block
-// counts, one scan block, then every block writes its run in order. The
-// scratch holds the block counts, the total and up to `cap` list entries;
-// the write pass never writes past `cap` (the host rejects a longer list).
+// Ascending list of the interface cells (read-out). The flags of the z
+// slabs that hold fluid are one run of memory (cells outside the fluid box
+// have no interface flag); it is cut into CMP_GRID blocks of 4 wavefronts,
+// and each wavefront walks its own run with 16 flags per lane, so a pass is
+// bound by the flags' memory and not by a block-wide scan per tile (256^3:
+// 92 us per pass before). Per-block counts, one scan block, then every
+// wavefront writes its run in order. The scratch holds the block counts and
+// up to `cap` list entries; the write pass never writes past `cap` (the host
+// rejects a longer list).
 struct ListScratch {
     int *counts;    // CMP_GRID ints
-    int *total;     // one int
     int32_t *list;  // cap ints
     int cap;
 };
+constexpr int LIST_LANE = 16, LIST_WAVE = 64 * LIST_LANE;
 
-__global__ __launch_bounds__(256) void k_ilist_count(const uint8_t *flags, const DevScalars *sc, int nx, int ny,
-                                                     ListScratch s)
+// Cells [c0, c1) of this wavefront, whole LIST_WAVE groups from a 16-byte
+// boundary.
+__device__ inline void list_run(const DevScalars *sc, int nx, int ny, int N, long long &c0, long long &c1)
 {
-    const CellRange range = CellRange::from(sc->fbox);
-    __shared__ int lw[4];
-    int t0, t1;
-    tile_range(range.size(), t0, t1);
-    int sum = 0;
-    for (int t = t0; t < t1; ++t) {
-        bool hit[4];
-        int idx[4];
-        const int c = cells_matching(flags, range, nx, ny, t * CMP_CELLS + threadIdx.x * 4, FL_IF, hit, idx);
-        int total;
-        block_exclusive_scan(c, lw, total);
-        sum += total;
-    }
-    if (threadIdx.x == 0) s.counts[blockIdx.x] = sum;
+    const CellRange box = CellRange::from(sc->fbox);
+    const long long a = ((long long)nx * ny * box.z0) / LIST_LANE * LIST_LANE;
+    const long long e = box.ez > 0 ? (long long)nx * ny * (box.z0 + box.ez) : a;
+    const long long groups = (e - a + LIST_WAVE - 1) / LIST_WAVE, waves = 4LL * gridDim.x;
+    const long long per = (groups + waves - 1) / waves, w = 4LL * blockIdx.x + (threadIdx.x >> 6);
+    c0 = a + w * per * LIST_WAVE;
+    c1 = min(min(c0 + per * LIST_WAVE, e), (long long)N);
 }
-
-__global__ __launch_bounds__(1024) void k_ilist_scan(ListScratch s, int nblocks)
+// Interface bits of the lane's 16 cells from cell i (bit k: cell i + k). The
+// flags' region is padded to 256 bytes, so the 16-byte load stays inside it.
+__device__ inline unsigned list_bits(const uint8_t *flags, long long i, long long end)
 {
-    __shared__ int lw[16];
-    int carry = 0;
-    for (int b0 = 0; b0 < nblocks; b0 += 1024) {
-        const int b = b0 + threadIdx.x;
-        const int v = b < nblocks ? s.counts[b] : 0;
-        int total;
-        const int ex = block_exclusive_scan(v, lw, total);
-        if (b < nblocks) s.counts[b] = carry + ex;
-        carry += total;
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) *s.total = carry;
-}
-
-__global__ __launch_bounds__(256) void k_ilist_write(const uint8_t *flags, const DevScalars *sc, int nx, int ny,
-                                                     ListScratch s)
-{
-    const CellRange range = CellRange::from(sc->fbox);
-    __shared__ int lw[4];
-    int t0, t1;
-    tile_range(range.size(), t0, t1);
-    int base = s.counts[blockIdx.x];
-    for (int t = t0; t < t1; ++t) {
-        bool hit[4];
-        int idx[4];
-        const int c = cells_matching(flags, range, nx, ny, t * CMP_CELLS + threadIdx.x * 4, FL_IF, hit, idx);
-        int total;
-        int pos = base + block_exclusive_scan(c, lw, total);
+    if (i >= end) return 0;
+    const uint4 v = *(const uint4 *)(flags + i);
+    const unsigned w[4] = {v.x, v.y, v.z, v.w};
+    unsigned m = 0;
 #pragma unroll
-        for (int k = 0; k < 4; ++k)
-            if (hit[k]) {
-                if (pos < s.cap) s.list[pos] = idx[k];
-                ++pos;
-            }
-        base += total;
+    for (int k = 0; k < 4; ++k) {
+        const unsigned t = (w[k] / FL_IF) & 0x01010101u;
+        m |= ((t | t >> 7 | t >> 14 | t >> 21) & 15u) << (4 * k);
+    }
+    const long long left = end - i;
+    return left < LIST_LANE ? m & ((1u << left) - 1u) : m;
+}
+__device__ inline int list_run_count(const uint8_t *flags, long long c0, long long c1)
+{
+    int n = 0;
+#pragma unroll 4
+    for (long long i = c0 + (threadIdx.x & 63) * LIST_LANE; i < c1; i += LIST_WAVE) n += __popc(list_bits(flags, i, c1));
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) n += __shfl_xor(n, d, 64);
+    return n;
+}
+
+__global__ __launch_bounds__(256) void k_ilist_count(const uint8_t *flags, const DevScalars *sc, int nx, int ny, int N,
+                                                     ListScratch s)
+{
+    __shared__ int cnt[4];
+    long long c0, c1;
+    list_run(sc, nx, ny, N, c0, c1);
+    const int n = list_run_count(flags, c0, c1);
+    if ((threadIdx.x & 63) == 0) cnt[threadIdx.x >> 6] = n;
+    __syncthreads();
+    if (threadIdx.x == 0) s.counts[blockIdx.x] = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+}
+
+__global__ __launch_bounds__(CMP_GRID) void k_ilist_scan(ListScratch s)
+{
+    __shared__ int lw[CMP_GRID / 64];
+    int total;
+    const int ex = block_exclusive_scan(s.counts[threadIdx.x], lw, total);
+    s.counts[threadIdx.x] = ex;
+}
+
+__global__ __launch_bounds__(256) void k_ilist_write(const uint8_t *flags, const DevScalars *sc, int nx, int ny, int N,
+                                                     ListScratch s)
+{
+    __shared__ int cnt[4];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    long long c0, c1;
+    list_run(sc, nx, ny, N, c0, c1);
+    const int mine = list_run_count(flags, c0, c1);
+    if (lane == 0) cnt[wave] = mine;
+    __syncthreads();
+    int pos = s.counts[blockIdx.x];
+    for (int w = 0; w < wave; ++w) pos += cnt[w];
+    if (mine == 0) return;
+    for (long long g = c0; g < c1; g += LIST_WAVE) {
+        const long long i = g + lane * LIST_LANE;
+        unsigned m = list_bits(flags, i, c1);
+        if (!__any(m != 0)) continue;
+        int x = __popc(m);
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const int y = __shfl_up(x, d, 64);
+            if (lane >= d) x += y;
+        }
+        int at = pos + x - __popc(m);
+        pos += __shfl(x, 63, 64);
+        while (m) {
+            const int k = __ffs(m) - 1;
+            m &= m - 1;
+            if (at < s.cap) s.list[at] = int(i) + k;
+            ++at;
+        }
     }
 }
 
-__global__ void k_read_flags(const uint8_t *flags, uint8_t *out, int N)
+// Cell types: 16 cells per thread where `out` is 16-byte aligned (VEC, the
+// last, partial group by single bytes), else one. GAS 1, LIQ 2, IF 4, OBST 8
+// become 0 .. 3: the logarithm, by bits 1-3 of each byte.
+__device__ inline unsigned type_codes(unsigned v)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= N) return;
-    const uint8_t t = flags[i] & FL_TYPE;
-    out[i] = t == FL_GAS ? 0 : (t == FL_LIQ ? 1 : (t == FL_IF ? 2 : 3));
+    const unsigned b1 = v >> 1 & 0x01010101u, b2 = v >> 2 & 0x01010101u, b3 = v >> 3 & 0x01010101u;
+    return b1 | b2 << 1 | b3 | b3 << 1;
+}
+template <bool VEC>
+__global__ __launch_bounds__(256) void k_read_flags(const uint8_t *flags, uint8_t *out, int N)
+{
+    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+    if constexpr (VEC) {
+        const long long i = 16 * t;
+        if (i + 16 <= N) {
+            const uint4 v = *(const uint4 *)(flags + i);
+            *(uint4 *)(out + i) = make_uint4(type_codes(v.x), type_codes(v.y), type_codes(v.z), type_codes(v.w));
+        } else {
+            for (long long k = i; k < N; ++k) out[k] = uint8_t(type_codes(flags[k]));
+        }
+    } else if (t < N) {
+        out[t] = uint8_t(type_codes(flags[t]));
+    }
 }
 
 // Mass: fixed partition of the cells over MASS_BLOCKS blocks, fixed
@@ -681,24 +756,60 @@ __global__ __launch_bounds__(1024) void k_mass_final(const double *part, DevScal
 // count, and the density sum and count of the inner liquid cells, those with
 // no gas or interface cell within a Euclidean distance of 2.5 cells
 // (periodic). part holds DIAG_VALUES rows of MASS_BLOCKS entries.
-template <class P>
-__device__ inline bool near_surface(const Fields<P> &F, int i)
+//
+// Which cells lie near a surface cell is found beforehand on bit rows (64
+// cells per word): the cells within a distance^2 of 6 are |dx| <= 2 in the 9
+// rows with |dy|, |dz| <= 1 and |dx| <= 1 in 12 rows more, so a word takes
+// the OR of each group's rows and two dilations along x. 81 flag loads per
+// cell took 1.5 ms of the 1.76 ms on 256^3. Both bit fields lie in the
+// staging area (8 N bytes; a row of nx >= 3 cells takes (nx + 63) / 64 words).
+__host__ __device__ inline int row_words(int nx) { return (nx + 63) / 64; }
+
+// Bits of the gas and interface cells, a wavefront per word.
+__global__ __launch_bounds__(256) void k_surface_bits(const uint8_t *flags, unsigned long long *surf, int nx, long long words)
 {
-    const int yz = i / F.nx, x = i - yz * F.nx, z = yz / F.ny, y = yz - z * F.ny;
+    const int lane = threadIdx.x & 63, wpr = row_words(nx);
+    for (long long w = blockIdx.x * 4LL + (threadIdx.x >> 6); w < words; w += gridDim.x * 4LL) {
+        const long long row = w / wpr;
+        const int x = int(w - row * wpr) * 64 + lane;
+        const bool on = x < nx && (flags[row * nx + x] & (FL_GAS | FL_IF));
+        const unsigned long long m = __ballot(on);
+        if (lane == 0) surf[w] = m;
+    }
+}
+
+// Bits of the cells with a surface cell within a distance^2 of 6 (periodic),
+// a thread per word. A word's row window is its own bits between the two
+// cells before and the two cells after them.
+__global__ __launch_bounds__(256) void k_near_bits(const unsigned long long *surf, unsigned long long *near, int nx, int ny,
+                                                   int nz, long long words)
+{
+    const long long w = blockIdx.x * 256LL + threadIdx.x;
+    if (w >= words) return;
+    const int wpr = row_words(nx), j = int(w % wpr), r = int(w / wpr), y = r % ny, z = r / ny;
+    const int len = min(64, nx - 64 * j);
+    const int xs[4] = {wrap_one(64 * j - 2, nx), wrap_one(64 * j - 1, nx), wrap_one(64 * j + len, nx),
+                       wrap_one(64 * j + len + 1, nx)};
+    typedef unsigned __int128 u128;
+    u128 win[2] = {0, 0};  // rows with |dx| <= 2, rows with |dx| <= 1
+#pragma unroll
     for (int dz = -2; dz <= 2; ++dz)
+#pragma unroll
         for (int dy = -2; dy <= 2; ++dy) {
-            const int row = F.nx * (wrap_any(y + dy, F.ny) + F.ny * wrap_any(z + dz, F.nz));
-            for (int dx = -2; dx <= 2; ++dx) {
-                if (dx * dx + dy * dy + dz * dz > 6) continue;
-                const uint8_t t = F.flags[row + wrap_any(x + dx, F.nx)] & FL_TYPE;
-                if (t == FL_GAS || t == FL_IF) return true;
-            }
+            const int left = 6 - dy * dy - dz * dz;
+            if (left < 0) continue;
+            const unsigned long long *row =
+                surf + ((long long)wrap_one(z + dz, nz) * ny + wrap_one(y + dy, ny)) * wpr;
+            auto bit = [&](int x) { return (u128)((row[x >> 6] >> (x & 63)) & 1); };
+            win[left >= 4 ? 0 : 1] |= bit(xs[0]) | bit(xs[1]) << 1 | (u128)row[j] << 2 | bit(xs[2]) << (len + 2) |
+                                      bit(xs[3]) << (len + 3);
         }
-    return false;
+    const u128 a = win[0], b = win[1];
+    near[w] = (unsigned long long)(a | a >> 1 | a >> 2 | a >> 3 | a >> 4 | b >> 1 | b >> 2 | b >> 3);
 }
 
 template <class P>
-__global__ __launch_bounds__(256) void k_diag_partial(Fields<P> F, double *part)
+__global__ __launch_bounds__(256) void k_diag_partial(Fields<P> F, const unsigned long long *near, double *part)
 {
     using T = typename P::T;
     __shared__ double s[DIAG_VALUES][256];
@@ -716,7 +827,9 @@ __global__ __launch_bounds__(256) void k_diag_partial(Fields<P> F, double *part)
         umax = fmax(umax, sp);
         usum += sp;
         nfl += 1.0;
-        if ((fl & FL_TYPE) == FL_LIQ && !near_surface(F, i)) {
+        const int row = i / F.nx, x = i - row * F.nx;
+        const bool close = near[(long long)row * row_words(F.nx) + (x >> 6)] >> (x & 63) & 1;
+        if ((fl & FL_TYPE) == FL_LIQ && !close) {
             rsum += r;
             nin += 1.0;
         }
@@ -1095,20 +1208,31 @@ int enqueue_init(fslbm_lattice *h, const double *fill, const uint8_t *obstacle)
 }
 
 template <class P>
-int do_read(fslbm_lattice *h, int what, double *out, int out_is_device)
+void launch_read(fslbm_lattice *h, int what, double *dst)
 {
     const Fields<P> F = make_fields<P>(h);
-    const int N = h->N;
-    const int comps = (what == RD_VEL || what == RD_NORMAL) ? 3 : 1;
-    double *staging = (double *)(h->ws + h->L.staging);
-    for (int c = 0; c < comps; ++c) {
-        double *dst = out_is_device ? out + (size_t)c * N : staging;
-        k_read<P><<<cell_blocks(N), 256, 0, h->stream>>>(F, h->rho_gas, h->bubble, what, c, dst);
-        HIP_OK(hipGetLastError());
-        if (!out_is_device)
-            HIP_OK(hipMemcpyAsync(out + (size_t)c * N, staging, sizeof(double) * N, hipMemcpyDeviceToHost, h->stream));
+    const bool moments = what == RD_PRESSURE || what == RD_VEL;
+    const dim3 g(moments ? cell_blocks(h->N) : (int)(((long long)h->N + 256 * READ_CELLS - 1) / (256 * READ_CELLS)));
+    switch (what) {
+#define FSLBM_RD(W) case W: k_read<P, W><<<g, 256, 0, h->stream>>>(F, h->rho_gas, h->bubble, dst); break;
+        FSLBM_RD(RD_FILL) FSLBM_RD(RD_PRESSURE) FSLBM_RD(RD_CURV) FSLBM_RD(RD_VEL)
+        FSLBM_RD(RD_NORMAL) FSLBM_RD(RD_PLIC) FSLBM_RD(RD_MASS)
+#undef FSLBM_RD
     }
-    HIP_OK(hipStreamSynchronize(h->stream));
+}
+
+// Enqueues the read-out; the caller synchronises (refresh_box).
+template <class P>
+int do_read(fslbm_lattice *h, int what, double *out, int out_is_device)
+{
+    const size_t N = h->N, comps = (what == RD_VEL || what == RD_NORMAL) ? 3 : 1;
+    // three components for the host go through the (scratch) destination PDF
+    // buffer, whose 19 planes hold at least 3 planes of doubles
+    double *dst = out;
+    if (!out_is_device) dst = (double *)(h->ws + (comps == 1 ? h->L.staging : (h->cur == 0 ? h->L.fB : h->L.fA)));
+    launch_read<P>(h, what, dst);
+    HIP_OK(hipGetLastError());
+    if (!out_is_device) HIP_OK(hipMemcpyAsync(out, dst, sizeof(double) * comps * N, hipMemcpyDeviceToHost, h->stream));
     return 0;
 }
 
@@ -1130,7 +1254,12 @@ int do_diagnostics(fslbm_lattice *h, double *out)
 {
     const Fields<P> F = make_fields<P>(h);
     double *part = (double *)(h->ws + h->L.part);
-    k_diag_partial<P><<<MASS_BLOCKS, 256, 0, h->stream>>>(F, part);
+    unsigned long long *surf = (unsigned long long *)(h->ws + h->L.staging);
+    const long long words = (long long)row_words(h->nx) * h->ny * h->nz;
+    unsigned long long *near = surf + words;
+    k_surface_bits<<<(int)std::min<long long>(16384, (words + 3) / 4), 256, 0, h->stream>>>(F.flags, surf, h->nx, words);
+    k_near_bits<<<(int)((words + 255) / 256), 256, 0, h->stream>>>(surf, near, h->nx, h->ny, h->nz, words);
+    k_diag_partial<P><<<MASS_BLOCKS, 256, 0, h->stream>>>(F, near, part);
     k_diag_final<<<1, 1024, 0, h->stream>>>(part, F.sc);
     HIP_OK(hipGetLastError());
     double v[DIAG_VALUES + 1];
@@ -2147,25 +2276,21 @@ int fslbm_read_flags(fslbm_t h, uint8_t *out, int out_is_device)
     const int N = h->N;
     uint8_t *flags = (uint8_t *)(h->ws + h->L.flags);
     uint8_t *dst = out_is_device ? out : (uint8_t *)(h->ws + h->L.staging);
-    k_read_flags<<<cell_blocks(N), 256, 0, h->stream>>>(flags, dst, N);
+    if ((reinterpret_cast<uintptr_t>(dst) & 15) == 0) k_read_flags<true><<<(N / 16 + 256) / 256, 256, 0, h->stream>>>(flags, dst, N);
+    else k_read_flags<false><<<cell_blocks(N), 256, 0, h->stream>>>(flags, dst, N);
     HIP_OK(hipGetLastError());
     if (!out_is_device) HIP_OK(hipMemcpyAsync(out, dst, N, hipMemcpyDeviceToHost, h->stream));
-    HIP_OK(hipStreamSynchronize(h->stream));
     return refresh_box(h);
 }
 
-// Runs the ordered compaction of the interface cells with the given
-// scratch and copies the count (and, with out, the list) to the host.
+// The number of interface cells (the device keeps it), and with out the
+// ordered compaction with the given scratch, copied to the host.
 static int read_ilist(fslbm_t h, const ListScratch &s, int32_t *out, int64_t capacity, int64_t *count)
 {
     const uint8_t *flags = (const uint8_t *)(h->ws + h->L.flags);
     const DevScalars *sc = (const DevScalars *)(h->ws + h->L.sc);
-    k_ilist_count<<<CMP_GRID, 256, 0, h->stream>>>(flags, sc, h->nx, h->ny, s);
-    k_ilist_scan<<<1, 1024, 0, h->stream>>>(s, CMP_GRID);
-    k_ilist_write<<<CMP_GRID, 256, 0, h->stream>>>(flags, sc, h->nx, h->ny, s);
-    HIP_OK(hipGetLastError());
     int n = 0;
-    HIP_OK(hipMemcpyAsync(&n, s.total, sizeof(int), hipMemcpyDeviceToHost, h->stream));
+    HIP_OK(hipMemcpyAsync(&n, &sc->icount, sizeof(int), hipMemcpyDeviceToHost, h->stream));
     HIP_OK(hipStreamSynchronize(h->stream));
     if (n > s.cap)
         return fail(FSLBM_E_SHAPE, "interface list has %d cells; the scratch of this call holds at most %d", n, s.cap);
@@ -2173,6 +2298,10 @@ static int read_ilist(fslbm_t h, const ListScratch &s, int32_t *out, int64_t cap
     if (!out) return 0;
     if (n > capacity) return fail(FSLBM_E_SHAPE, "interface list has %d entries, capacity %lld", n, (long long)capacity);
     if (n > 0) {
+        k_ilist_count<<<CMP_GRID, 256, 0, h->stream>>>(flags, sc, h->nx, h->ny, h->N, s);
+        k_ilist_scan<<<1, CMP_GRID, 0, h->stream>>>(s);
+        k_ilist_write<<<CMP_GRID, 256, 0, h->stream>>>(flags, sc, h->nx, h->ny, h->N, s);
+        HIP_OK(hipGetLastError());
         HIP_OK(hipMemcpyAsync(out, s.list, sizeof(int32_t) * n, hipMemcpyDeviceToHost, h->stream));
         HIP_OK(hipStreamSynchronize(h->stream));
     }
@@ -2187,7 +2316,6 @@ int fslbm_read_interface_list(fslbm_t h, int32_t *out, int64_t capacity, int64_t
     char *stg = h->ws + h->L.staging;
     ListScratch s;
     s.counts = (int *)(h->ws + h->L.counts);
-    s.total = (int *)stg;
     s.list = (int32_t *)(stg + 256);
     s.cap = h->N;
     return read_ilist(h, s, out, capacity, count);
@@ -2195,13 +2323,13 @@ int fslbm_read_interface_list(fslbm_t h, int32_t *out, int64_t capacity, int64_t
 
 // ------------------------------------------- allocation-free read-out
 // Scratch of fslbm_read_interface_list_noalloc: a file-scope device array
-// of fixed size (block counts, total, up to NOALLOC_LIST_CAP list entries).
+// of fixed size (block counts, up to NOALLOC_LIST_CAP list entries).
 // Every device the library runs on holds its own copy until the process
 // ends. Host code never passes the symbol itself to a kernel: it uses the
 // per-device address that hipGetSymbolAddress returns on that device.
 constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(16) << 20;
 constexpr int NOALLOC_LIST_CAP = int((NOALLOC_SCRATCH_BYTES - 2048) / 4);
-static_assert(CMP_GRID * sizeof(int) <= 1024, "block counts must fit below the total at byte 1024");
+static_assert(CMP_GRID * sizeof(int) <= 2048, "block counts must fit below the list at byte 2048");
 static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 
 namespace {
@@ -2238,7 +2366,6 @@ int fslbm_read_interface_list_noalloc(fslbm_t h, int32_t *out, int64_t capacity,
     if (!rc) {
         ListScratch s;
         s.counts = (int *)base;  // CMP_GRID ints
-        s.total = (int *)(base + 1024);
         s.list = (int32_t *)(base + 2048);
         s.cap = NOALLOC_LIST_CAP;
         rc = read_ilist(h, s, out, capacity, count);

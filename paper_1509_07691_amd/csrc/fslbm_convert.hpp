@@ -63,12 +63,6 @@ __device__ inline const int32_t *interface_list(const Fields<P> &F)
 // old-list cell that leaves the layer).
 __device__ inline bool is_new(uint32_t mk, uint32_t tag) { return (mk & ~3u) == tag && (mk & 3u) != 3u; }
 
-__device__ inline int wrap_any(int v, int n)
-{
-    v %= n;
-    return v < 0 ? v + n : v;
-}
-
 __device__ inline int wrap_one(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 
 // Rules 2 and 3, one wavefront per cell that the stream-collide listed as
