@@ -900,7 +900,7 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
 
     // ---- forward fit, rows split over the lanes
     LsqrSums S;
-    for (int s = lane; s < 27; s += L) lsqr_cell_rows(V, prm, fr, s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1, S);
+    for (int s = lane; s < 27; s += L) lsqr_cell_rows(V, fr, s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1, S);
     if (has_obst)
         for (int s = lane; s < 27; s += L) lsqr_contact_rows(V, prm, fr, s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1, S);
     for (int e = 0; e < 15; ++e) S.G[e] = group_sum<L>(S.G[e]);

@@ -57,7 +57,7 @@ size_t fbytes(int prec)
 size_t rbytes(int prec) { return prec == P_F64 ? 8 : 4; }
 
 struct Layout {
-    size_t fA, fB, flags, conv, near, mark, m, rho, phi, K, nrm, plic, cnrm, ilist, olist, wlist, newlist, ilist_tmp, clist,
+    size_t fA, fB, flags, conv, near, mark, m, rho, phi, K, nrm, plic, cnrm, ilist, olist, wlist, newlist, ilist_tmp, clist, wpos, wdir, contact,
         staging,
         counts, part, sc, total;
 };
@@ -72,6 +72,11 @@ constexpr int DIAG_VALUES = 5;  // partial sums per block of the diagnostics
 // 3514 us with the 1024-element gap and 3562 without (F16 1877 and 1891; a
 // 4096-element gap slowed F16 to 1976).
 long long plane_stride(long long N) { return (N + 63) / 64 * 64 + 1024; }
+
+// Wall-list cells whose contact data are kept (LSQR). A fifth of the cells:
+// with walls of a cell or two around a fluid, the cells next to them are far
+// fewer; a lattice with more (a porous body) computes the data in each fit.
+size_t contact_cap(size_t N) { return std::max<size_t>(1, N / 5); }
 
 Layout make_layout(int nx, int ny, int nz, int prec)
 {
@@ -104,6 +109,9 @@ Layout make_layout(int nx, int ny, int nz, int prec)
     L.newlist = take(4 * N);
     L.ilist_tmp = take(4 * N);
     L.clist = take(4 * N);
+    L.wpos = take(4 * N);
+    L.wdir = take(4 * contact_cap(N));
+    L.contact = take(6 * 8 * contact_cap(N));
     L.staging = take(8 * N + 512);  // N doubles for read-outs; the ordered interface list (N ints)
     L.counts = take(4 * (size_t)CMP_GRID);  // one count per compaction block (fixed grid)
     L.part = take(8 * (DIAG_VALUES * MASS_BLOCKS + 8));  // mass, bubble volume and diagnostics partials
@@ -182,6 +190,7 @@ struct fslbm_lattice {
     int N;
     int NS;  // plane stride of the distribution buffers
     int box_blocks;  // SC_BLOCK-cell chunks of the fluid box when last read back (grid of the bulk stream-collide)
+    int wcount;  // wall-list cells when last read back (-1: not yet)
     long long box_cells, boundary_cells;  // fluid-box cells, interface + wall-list cells (last read back)
     int device;      // device that holds the workspace
     int strong_wetting;  // 1: contact angles below 45 deg are accepted (FSLBM_OPT_STRONG_WETTING)
@@ -235,6 +244,11 @@ Params make_params(const fslbm_lattice *h)
     return p;
 }
 
+bool keeps_contact(const fslbm_lattice *h)
+{
+    return h->curv == FSLBM_CURV_LSQR && h->wcount >= 0 && (size_t)h->wcount <= contact_cap(h->N);
+}
+
 template <class P>
 Fields<P> make_fields(const fslbm_lattice *h)
 {
@@ -265,6 +279,9 @@ Fields<P> make_fields(const fslbm_lattice *h)
     F.newlist = (int32_t *)at(L.newlist);
     F.ilist_tmp = (int32_t *)at(L.ilist_tmp);
     F.clist = (int32_t *)at(L.clist);
+    F.wpos = (int32_t *)at(L.wpos);
+    F.wdir = (int32_t *)at(L.wdir);
+    F.contact = keeps_contact(h) ? (double *)at(L.contact) : nullptr;
     F.counts = (int *)at(L.counts);
     F.part = (double *)at(L.part);
     F.sc = (DevScalars *)at(L.sc);
@@ -935,8 +952,9 @@ int enqueue_geometry(const fslbm_batch *b, const Batch<P> &A, int maxN, int eos 
     const unsigned n = (unsigned)b->hs.size();
     const hipStream_t st = bstream(b);
     const dim3 tg(std::min(GEOM_GRID, std::max(1, maxN / 512)), n);
-    bool any_fd = false, any_fd_wall = false, any_lsqr = false, any_tr = false;
+    bool any_fd = false, any_fd_wall = false, any_lsqr = false, any_tr = false, stored = true;
     for (auto *h : b->hs) {
+        if (h->curv == FSLBM_CURV_LSQR) stored &= keeps_contact(h);
         any_fd |= h->curv == FSLBM_CURV_FD;
         any_fd_wall |= h->curv == FSLBM_CURV_FD && h->ocount0 > 0;
         any_lsqr |= h->curv == FSLBM_CURV_LSQR;
@@ -952,7 +970,8 @@ int enqueue_geometry(const fslbm_batch *b, const Batch<P> &A, int maxN, int eos 
     if (any_fd && any_plic) k_geometry_mixed<P><<<tg, 256, 0, st>>>(A, eos);
     else if (any_fd) k_geometry_fd<P><<<tg, 256, 0, st>>>(A, eos);
     else k_normals_plic<P><<<dim3(batch_list_blocks(b, 256), n), 256, 0, st>>>(A, eos);
-    if (any_lsqr) k_curv_lsqr4<P><<<cg4, 256, 0, st>>>(A);
+    if (any_lsqr && stored) k_curv_lsqr4<P, true><<<cg4, 256, 0, st>>>(A);
+    else if (any_lsqr) k_curv_lsqr4<P, false><<<cg4, 256, 0, st>>>(A);
     if (any_tr) k_curv_tr<P><<<cgt, 256, 0, st>>>(A);
     HIP_OK(hipGetLastError());
     return 0;
@@ -1168,6 +1187,17 @@ int batch_step_once(fslbm_batch *b)
     return 0;
 }
 
+// Positions and directions of the wall-list cells (static with the list).
+void enqueue_wall_index(fslbm_lattice *h)
+{
+    const Layout &L = h->L;
+    char *w = h->ws;
+    k_wall_index<<<list_blocks(h->N), 256, 0, h->stream>>>((const uint8_t *)(w + L.flags), (const int32_t *)(w + L.wlist),
+                                                          (int32_t *)(w + L.wpos), (int32_t *)(w + L.wdir),
+                                                          (int)contact_cap(h->N), (const DevScalars *)(w + L.sc), h->nx,
+                                                          h->ny, h->nz);
+}
+
 template <class P>
 int enqueue_init(fslbm_lattice *h, const double *fill, const uint8_t *obstacle)
 {
@@ -1199,6 +1229,7 @@ int enqueue_init(fslbm_lattice *h, const double *fill, const uint8_t *obstacle)
     int rc = enqueue_compaction<P>(&h->self, A, maxN, 1, 1);
     if (!rc) rc = enqueue_compaction<P>(&h->self, A, maxN, 2, 1);
     if (rc) return rc;
+    enqueue_wall_index(h);
     k_fill_bytes<<<std::min(4096, cell_blocks(N)), 256, 0, h->stream>>>(F.conv, N, 0);
     rc = enqueue_compaction<P>(&h->self, A, maxN, 0, 1);
     if (rc) return rc;
@@ -1455,6 +1486,10 @@ int refresh_box(fslbm_lattice *h)
     const int blocks = xcd_grid((cells + SC_BLOCK - 1) / SC_BLOCK);
     h->boundary_cells = (long long)sc.icount + sc.wcount;
     h->box_cells = cells;
+    if (sc.wcount != h->wcount) {
+        h->wcount = sc.wcount;
+        h->version += 1;
+    }
     if (blocks != h->box_blocks) {
         h->box_blocks = blocks;
         h->version += 1;
@@ -2042,6 +2077,7 @@ int fslbm_create(int nx, int ny, int nz, int precision, int curv_model, const do
     h->box_blocks = xcd_grid(((long long)N + SC_BLOCK - 1) / SC_BLOCK);
     h->box_cells = N;
     h->boundary_cells = N;
+    h->wcount = -1;
     int rc = dispatch<OpInit>(h, fill, obstacle);
     if (!rc) {
         int ic = 0, oc = 0;
@@ -2484,6 +2520,7 @@ int fslbm_load_state(fslbm_t h, const void *src, size_t bytes)
     h->epoch += 1;
     h->version += 1;
     k_list_reset<<<1, 1, 0, h->stream>>>((DevScalars *)(h->ws + h->L.sc));
+    enqueue_wall_index(h);  // the state brings its own wall list
     HIP_OK(hipGetLastError());
     HIP_OK(hipStreamSynchronize(h->stream));
     // the loaded state brings its own obstacle list (launch sizing only)

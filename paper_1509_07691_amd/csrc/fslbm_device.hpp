@@ -392,6 +392,8 @@ template <class P> struct Fields {
     R *cnrm;           // FD wetting: contact normal of obstacle cells (3 planes, 0 = none)
     int32_t *ilist, *olist;  // read the interface list through interface_list()
     int32_t *wlist;    // static: non-obstacle cells with an obstacle D3Q19 neighbour
+    int32_t *wpos, *wdir;  // static: position in wlist of a wlist cell; per wlist entry the sum of its obstacle directions
+    double *contact;   // LSQR: contact data per wlist entry (store_contact), or null where there is no room for them
     int32_t *newlist, *ilist_tmp;  // new interface cells; the interface list's other buffer
     int32_t *clist;    // cells that fill or empty in this step (nconv entries)
     int *counts;       // per-block counts of the list compaction

@@ -159,72 +159,6 @@ __host__ __device__ inline G plic_offset(G nx, G ny, G nz, G phi)
 }
 
 // --------------------------------------------------------- LSQR model
-// Normal equations of the least-squares fit, accumulated row by row.
-template <int C> struct Gram {
-    double G[C][C];
-    double g[C];
-    __host__ __device__ inline Gram()
-    {
-#pragma unroll
-        for (int r = 0; r < C; ++r) {
-            g[r] = 0.0;
-#pragma unroll
-            for (int c = 0; c < C; ++c) G[r][c] = 0.0;
-        }
-    }
-    __host__ __device__ inline void add(const double (&a)[C], double b)
-    {
-#pragma unroll
-        for (int r = 0; r < C; ++r) {
-            g[r] += a[r] * b;
-#pragma unroll
-            for (int c = 0; c <= r; ++c) G[r][c] += a[r] * a[c];
-        }
-    }
-    // Cholesky solve; fails when a pivot falls below 1e-12 * trace(G)
-    // (rank deficiency of the row matrix).
-    __host__ __device__ inline bool solve(double (&x)[C]) const
-    {
-        double tr = 0.0;
-#pragma unroll
-        for (int r = 0; r < C; ++r) tr += G[r][r];
-        if (!(tr > 0.0)) return false;
-        double L[C][C];
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-            double d = G[c][c];
-#pragma unroll
-            for (int j = 0; j < c; ++j) d -= L[c][j] * L[c][j];
-            if (!(d >= 1e-12 * tr)) return false;
-            L[c][c] = sqrt(d);
-#pragma unroll
-            for (int r = c + 1; r < C; ++r) {
-                double s = G[r][c];
-#pragma unroll
-                for (int j = 0; j < c; ++j) s -= L[r][j] * L[c][j];
-                L[r][c] = s / L[c][c];
-            }
-        }
-        double y[C];
-#pragma unroll
-        for (int r = 0; r < C; ++r) {
-            double s = g[r];
-#pragma unroll
-            for (int j = 0; j < r; ++j) s -= L[r][j] * y[j];
-            y[r] = s / L[r][r];
-        }
-#pragma unroll
-        for (int r = C - 1; r >= 0; --r) {
-            double s = y[r];
-#pragma unroll
-            for (int j = r + 1; j < C; ++j) s -= L[j][r] * x[j];
-            x[r] = s / L[r][r];
-        }
-        return true;
-    }
-};
-
-
 __host__ __device__ inline double dot(const double (&a)[3], const double (&b)[3]) { return a[0] * b[0] + a[1] * b[1] + a[2] * b[2]; }
 
 constexpr int TILE = 8;
@@ -622,51 +556,119 @@ __device__ inline void lsqr_stage(const Fields<P> &F, int x, int y, int z, int l
     }
 }
 
-// Contact point and contact normal of the contact-line cell at offset d from
-// the centre (eqs. contactNormal, contactConstraint; Fig. contactPoint): the
+// What a contact-line cell j contributes whatever the centre of the fit
+// (eqs. contactNormal, contactConstraint; Fig. contactPoint): its contact
+// normal mh, and the step tg from its PLIC point to the contact point, the
 // point of (PLIC plane) ∩ (wall plane) nearest to the PLIC point, reached
 // along the wall normal projected onto the PLIC plane; the wall plane lies
 // half a cell from the cell centre along the wall normal (the bounce-back
-// wall is half-way between nodes). Returns false when the condition is
-// skipped.
+// wall is half-way between nodes). nj, aj: the cell's normal and PLIC
+// offset; (sx, sy, sz): the sum of the directions to its obstacle
+// neighbours. mh = 0 where the condition is skipped.
+__host__ __device__ __forceinline__ void contact_point(const double (&nj)[3], double aj, int sx, int sy, int sz,
+                                                       const Params &prm, double (&mh)[3], double (&tg)[3])
+{
+    mh[0] = mh[1] = mh[2] = tg[0] = tg[1] = tg[2] = 0.0;
+    if (nj[0] == 0.0 && nj[1] == 0.0 && nj[2] == 0.0) return;
+    const double lw = sqrt(double(sx * sx + sy * sy + sz * sz));
+    if (!(lw > 0.0)) return;
+    const double nw[3] = {sx / lw, sy / lw, sz / lw};
+    const double nn = dot(nj, nw);
+    double nt[3] = {nj[0] - nn * nw[0], nj[1] - nn * nw[1], nj[2] - nn * nw[2]};
+    const double lt = sqrt(dot(nt, nt));
+    if (lt < 1e-12) return;
+    nt[0] /= lt; nt[1] /= lt; nt[2] /= lt;
+    const double g[3] = {nw[0] - nn * nj[0], nw[1] - nn * nj[1], nw[2] - nn * nj[2]};
+    const double gn = dot(g, nw);
+    if (gn < 1e-12) return;
+    const double pj[3] = {aj * nj[0], aj * nj[1], aj * nj[2]};
+    const double t = (0.5 - dot(pj, nw)) / gn;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        mh[k] = nw[k] * prm.cos_theta + nt[k] * prm.sin_theta;
+        tg[k] = t * g[k];
+    }
+}
+
+// The condition of the contact-line cell at offset d from the centre in the
+// centre's frame; false where it is skipped.
+__host__ __device__ __forceinline__ bool contact_row(const double (&mh)[3], const double (&tg)[3], int dx, int dy, int dz,
+                                                     const double (&nj)[3], double aj, const double (&pc)[3],
+                                                     const double (&nc)[3], const double (&tu)[3], const double (&tv)[3],
+                                                     double &uc, double &vc, double &ru, double &rv)
+{
+    const double mu = dot(mh, tu), mv = dot(mh, tv), mn = dot(mh, nc);
+    if (fabs(mn) < 1e-6) return false;
+    const double r[3] = {dx + aj * nj[0] + tg[0] - pc[0], dy + aj * nj[1] + tg[1] - pc[1], dz + aj * nj[2] + tg[2] - pc[2]};
+    uc = dot(r, tu);
+    vc = dot(r, tv);
+    ru = -mu / mn;
+    rv = -mv / mn;
+    return true;
+}
+
 template <class View>
 __host__ __device__ __forceinline__ bool contact_condition(const View &V, int dx, int dy, int dz, const double (&pc)[3],
                                          const double (&nc)[3], const double (&tu)[3], const double (&tv)[3],
                                          const Params &prm, double &uc, double &vc, double &ru, double &rv)
 {
-    double nj[3];
+    double nj[3], mh[3], tg[3];
     V.normal(dx, dy, dz, nj);
-    if (nj[0] == 0.0 && nj[1] == 0.0 && nj[2] == 0.0) return false;
     int sx = 0, sy = 0, sz = 0;
 #pragma unroll
     for (int q = 1; q < NQ; ++q)
         if (V.flag(dx + dir_x(q), dy + dir_y(q), dz + dir_z(q)) & FL_OBST) {
             sx += dir_x(q); sy += dir_y(q); sz += dir_z(q);
         }
-    const double lw = sqrt(double(sx * sx + sy * sy + sz * sz));
-    if (!(lw > 0.0)) return false;
-    const double nw[3] = {sx / lw, sy / lw, sz / lw};
-    const double nn = dot(nj, nw);
-    double nt[3] = {nj[0] - nn * nw[0], nj[1] - nn * nw[1], nj[2] - nn * nw[2]};
-    const double lt = sqrt(dot(nt, nt));
-    if (lt < 1e-12) return false;
-    nt[0] /= lt; nt[1] /= lt; nt[2] /= lt;
-    const double mh[3] = {nw[0] * prm.cos_theta + nt[0] * prm.sin_theta, nw[1] * prm.cos_theta + nt[1] * prm.sin_theta,
-                          nw[2] * prm.cos_theta + nt[2] * prm.sin_theta};
-    const double g[3] = {nw[0] - nn * nj[0], nw[1] - nn * nj[1], nw[2] - nn * nj[2]};
-    const double gn = dot(g, nw);
-    if (gn < 1e-12) return false;
     const double aj = V.plic(dx, dy, dz);
-    const double pj[3] = {aj * nj[0], aj * nj[1], aj * nj[2]};
-    const double t = (0.5 - dot(pj, nw)) / gn;
-    const double r[3] = {dx + pj[0] + t * g[0] - pc[0], dy + pj[1] + t * g[1] - pc[1], dz + pj[2] + t * g[2] - pc[2]};
-    uc = dot(r, tu);
-    vc = dot(r, tv);
-    const double mu = dot(mh, tu), mv = dot(mh, tv), mn = dot(mh, nc);
-    if (fabs(mn) < 1e-6) return false;
-    ru = -mu / mn;
-    rv = -mv / mn;
-    return true;
+    contact_point(nj, aj, sx, sy, sz, prm, mh, tg);
+    return contact_row(mh, tg, dx, dy, dz, nj, aj, pc, nc, tu, tv, uc, vc, ru, rv);
+}
+
+// The directions to the obstacle neighbours of a wall-list cell, summed
+// (static), packed in one word.
+__host__ __device__ inline int pack_dir(int sx, int sy, int sz) { return (sx + 32) | (sy + 32) << 8 | (sz + 32) << 16; }
+__host__ __device__ inline void unpack_dir(int p, int &sx, int &sy, int &sz)
+{
+    sx = (p & 255) - 32;
+    sy = (p >> 8 & 255) - 32;
+    sz = (p >> 16 & 255) - 32;
+}
+// Position of each wall-list cell in the list, and its direction sum.
+__global__ __launch_bounds__(256) void k_wall_index(const uint8_t *flags, const int32_t *wlist, int32_t *wpos, int32_t *wdir,
+                                                    int cap, const DevScalars *sc, int nx, int ny, int nz)
+{
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < sc->wcount; k += gridDim.x * 256) {
+        const int i = wlist[k];
+        wpos[i] = k;
+        if (k >= cap) continue;
+        const Nbr nb(i, nx, ny, nz);
+        int sx = 0, sy = 0, sz = 0;
+#pragma unroll
+        for (int q = 1; q < NQ; ++q)
+            if (flags[nb.at(dir_x(q), dir_y(q), dir_z(q))] & FL_OBST) { sx += dir_x(q); sy += dir_y(q); sz += dir_z(q); }
+        wdir[k] = pack_dir(sx, sy, sz);
+    }
+}
+
+// contact_point of interface cell i (its normal n and PLIC offset a as they
+// are stored), kept for every fit whose block holds the cell.
+template <class P>
+__device__ inline void store_contact(const Fields<P> &F, const Params &prm, int i, const typename P::R (&n)[3],
+                                     typename P::R a)
+{
+    const int w = F.wpos[i];
+    int sx, sy, sz;
+    unpack_dir(F.wdir[w], sx, sy, sz);
+    const double nj[3] = {double(n[0]), double(n[1]), double(n[2])};
+    double mh[3], tg[3];
+    contact_point(nj, double(a), sx, sy, sz, prm, mh, tg);
+    double *c = F.contact + 6 * (size_t)w;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        c[k] = mh[k];
+        c[3 + k] = tg[k];
+    }
 }
 
 // Frame, PLIC point and wetting state of the centre of view V (Sec. II.C):
@@ -679,11 +681,9 @@ struct LsqrFrame {
     double huc, hvc, hu, hv;
 };
 
-// Completes a frame whose centre normal f.nc and validity f.ok are set,
-// given whether the block holds an obstacle cell.
-template <class View>
-__host__ __device__ __forceinline__ void lsqr_frame_finish(const View &V, const Params &prm, LsqrFrame &f,
-                                                           bool has_obst)
+// The axes and the PLIC point of a frame whose centre normal f.nc and
+// validity f.ok are set (ac: the centre's PLIC offset); no hard constraint.
+__host__ __device__ __forceinline__ void lsqr_frame_axes(LsqrFrame &f, double ac, bool has_obst)
 {
     f.has_obst = has_obst;
     f.hard = false;
@@ -702,27 +702,7 @@ __host__ __device__ __forceinline__ void lsqr_frame_finish(const View &V, const 
     f.tv[0] = nc[1] * f.tu[2] - nc[2] * f.tu[1];
     f.tv[1] = nc[2] * f.tu[0] - nc[0] * f.tu[2];
     f.tv[2] = nc[0] * f.tu[1] - nc[1] * f.tu[0];
-    const double ac = V.plic(0, 0, 0);
     f.pc[0] = ac * nc[0]; f.pc[1] = ac * nc[1]; f.pc[2] = ac * nc[2];
-    if (f.has_obst && (V.flag(0, 0, 0) & FL_NEAR_OBST))
-        f.hard = contact_condition(V, 0, 0, 0, f.pc, f.nc, f.tu, f.tv, prm, f.huc, f.hvc, f.hu, f.hv);
-}
-
-template <class View>
-__host__ __device__ __forceinline__ LsqrFrame lsqr_frame(const View &V, const Params &prm)
-{
-    LsqrFrame f;
-    V.normal(0, 0, 0, f.nc);
-    f.ok = !(f.nc[0] == 0.0 && f.nc[1] == 0.0 && f.nc[2] == 0.0);
-    bool has_obst = false;
-#pragma unroll
-    for (int c = -1; c <= 1; ++c)
-#pragma unroll
-        for (int b = -1; b <= 1; ++b)
-#pragma unroll
-            for (int a = -1; a <= 1; ++a) has_obst |= (V.flag(a, b, c) & FL_OBST) != 0;
-    lsqr_frame_finish(V, prm, f, has_obst);
-    return f;
 }
 
 // Cholesky solve of a C x C system held as a packed lower triangle
@@ -808,23 +788,34 @@ struct LsqrSums {
     }
 };
 
-// Rows contributed by the block cell at offset (a, b, c): its PLIC point
-// (interface cells other than the centre) and, for contact-line cells other
-// than the centre, the two rows of the gradient condition.
-template <class View>
-__host__ __device__ __forceinline__ void lsqr_cell_rows(const View &V, const Params &prm, const LsqrFrame &f, int a, int b,
-                                               int c, LsqrSums &S)
+// The row of the PLIC point (normal nj, offset aj) of the block cell at
+// offset (a, b, c), an interface cell other than the centre.
+__host__ __device__ __forceinline__ void lsqr_data_row(const LsqrFrame &f, int a, int b, int c, const double (&nj)[3],
+                                                       double aj, LsqrSums &S)
 {
-    if (a == 0 && b == 0 && c == 0) return;
-    const uint8_t fj = V.flag(a, b, c);
-    if (!(fj & FL_IF)) return;
-    double nj[3];
-    V.normal(a, b, c, nj);
-    if (nj[0] == 0.0 && nj[1] == 0.0 && nj[2] == 0.0) return;
-    const double aj = V.plic(a, b, c);
     const double r[3] = {a + aj * nj[0] - f.pc[0], b + aj * nj[1] - f.pc[1], c + aj * nj[2] - f.pc[2]};
     const double u = dot(r, f.tu), v = dot(r, f.tv), w = dot(r, f.nc);
     S.add(f, u * u, v * v, u * v, u, v, w);
+}
+// The two rows of the gradient condition of a contact-line cell other than
+// the centre.
+__host__ __device__ __forceinline__ void lsqr_contact_row(const LsqrFrame &f, double uc, double vc, double ru, double rv,
+                                                          LsqrSums &S)
+{
+    S.add(f, 2.0 * uc, 0.0, vc, 1.0, 0.0, ru);
+    S.add(f, 0.0, 2.0 * vc, uc, 0.0, 1.0, rv);
+}
+
+// Both for the block cell at offset (a, b, c) of a view.
+template <class View>
+__host__ __device__ __forceinline__ void lsqr_cell_rows(const View &V, const LsqrFrame &f, int a, int b, int c, LsqrSums &S)
+{
+    if (a == 0 && b == 0 && c == 0) return;
+    if (!(V.flag(a, b, c) & FL_IF)) return;
+    double nj[3];
+    V.normal(a, b, c, nj);
+    if (nj[0] == 0.0 && nj[1] == 0.0 && nj[2] == 0.0) return;
+    lsqr_data_row(f, a, b, c, nj, V.plic(a, b, c), S);
 }
 
 template <class View>
@@ -835,9 +826,7 @@ __host__ __device__ __forceinline__ void lsqr_contact_rows(const View &V, const 
     const uint8_t fj = V.flag(a, b, c);
     if (!((fj & FL_IF) && (fj & FL_NEAR_OBST))) return;
     double uc, vc, ru, rv;
-    if (!contact_condition(V, a, b, c, f.pc, f.nc, f.tu, f.tv, prm, uc, vc, ru, rv)) return;
-    S.add(f, 2.0 * uc, 0.0, vc, 1.0, 0.0, ru);
-    S.add(f, 0.0, 2.0 * vc, uc, 0.0, 1.0, rv);
+    if (contact_condition(V, a, b, c, f.pc, f.nc, f.tu, f.tv, prm, uc, vc, ru, rv)) lsqr_contact_row(f, uc, vc, ru, rv, S);
 }
 
 // Solve the normal equations (model choice as described above) and return
@@ -884,33 +873,18 @@ __host__ __device__ __forceinline__ double lsqr_solve_curvature(const LsqrFrame 
     return 2.0 * (A * (1.0 + I * I) + Bq * (1.0 + H * H) - C * H * I) / (gg * sqrt(gg));
 }
 
-// K = 2 kappa of the least-squares quadric at the centre of view V, rows
-// accumulated in block order (data rows, then contact rows).
-template <class View>
-__host__ __device__ inline double lsqr_curvature(const View &V, const Params &prm)
-{
-    const LsqrFrame f = lsqr_frame(V, prm);
-    if (!f.ok) return 0.0;
-    LsqrSums S;
-    for (int c = -1; c <= 1; ++c)
-        for (int b = -1; b <= 1; ++b)
-            for (int a = -1; a <= 1; ++a) lsqr_cell_rows(V, prm, f, a, b, c, S);
-    if (f.has_obst)
-        for (int c = -1; c <= 1; ++c)
-            for (int b = -1; b <= 1; ++b)
-                for (int a = -1; a <= 1; ++a) lsqr_contact_rows(V, prm, f, a, b, c, S);
-    return lsqr_solve_curvature(f, S);
-}
-
-// Normals and PLIC points of the interface cells (LSQR model).
+// Normals and PLIC points of the interface cells (LSQR and TR models), and
+// the contact data of those next to a wall where it is kept (LSQR).
 template <class P>
-__device__ inline void normals_plic_list(const Fields<P> &F)
+__device__ inline void normals_plic_list(const Fields<P> &F, const Params &prm)
 {
     using G = typename P::G;
     const int n = list_count(F.sc);
+    const int32_t *list = interface_list(F);
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
-        const int i = interface_list(F)[k];
+        const int i = list[k];
         const Nbr nb(i, F.nx, F.ny, F.nz);
+        const uint8_t fl = F.flags[i];
         G gx = 0, gy = 0, gz = 0;
 #pragma unroll
         for (int a = -1; a <= 1; ++a)
@@ -926,6 +900,7 @@ __device__ inline void normals_plic_list(const Fields<P> &F)
         const bool ok = nrm[0] != G(0) || nrm[1] != G(0) || nrm[2] != G(0);
         const G a = ok ? plic_offset<G>(nrm[0], nrm[1], nrm[2], G(F.phi[i])) : G(0);
         store_normal(F, i, nrm, a);
+        if (F.contact && (fl & FL_NEAR_OBST)) store_contact<P>(F, prm, i, nrm, a);
     }
 }
 
@@ -934,7 +909,7 @@ __global__ __launch_bounds__(256) void k_normals_plic(const Batch<P> B, int eos)
 {
     end_of_step(B.f[blockIdx.y].sc, eos);
     if (B.p[blockIdx.y].curv == 0) return;  // LSQR and TR
-    normals_plic_list(B.f[blockIdx.y]);
+    normals_plic_list(B.f[blockIdx.y], B.p[blockIdx.y]);
 }
 
 // First geometry launch of a batch that mixes the models: FD lattices run
@@ -945,70 +920,112 @@ __global__ __launch_bounds__(256) void k_geometry_mixed(const Batch<P> B, int eo
 {
     end_of_step(B.f[blockIdx.y].sc, eos);
     if (B.p[blockIdx.y].curv == 0) geometry_fd_tiles(B.f[blockIdx.y]);
-    else normals_plic_list(B.f[blockIdx.y]);
-}
-
-template <class P>
-__global__ __launch_bounds__(256) void k_curv_lsqr(const Batch<P> B)
-{
-    const Params &prm = B.p[blockIdx.y];
-    if (prm.curv != 1) return;
-    const Fields<P> &F = B.f[blockIdx.y];
-    using R = typename P::R;
-    const int n = list_count(F.sc);
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
-        const int i = interface_list(F)[k];
-        const int yz = i / F.nx, x = i - yz * F.nx, z = yz / F.ny, y = yz - z * F.ny;
-        const LsqrView<P> V{F, x, y, z};
-        F.K[i] = R(lsqr_curvature(V, prm));
-    }
+    else normals_plic_list(B.f[blockIdx.y], B.p[blockIdx.y]);
 }
 
 // LSQR curvature with 4 lanes per interface cell (64 cells per workgroup):
-// lane l of a group scans the block cells s = l, l + 4, ... (s = 0..26,
-// x fastest) for obstacles and adds their data and contact rows; the sums
-// are reduced over the 4 lanes by an xor butterfly (a fixed order, the same
-// result on every lane) and every lane solves the same system. Limited to
-// 168 VGPRs for 3 waves per SIMD (a 20-byte spill): this latency-bound
-// gather runs faster than at 2 waves with no spill.
-template <class P>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k_curv_lsqr4(const Batch<P> B)
+// lane l of a group takes the block cells s = l, l + 4, ... (s = 0..26,
+// x fastest): obstacles, data rows, contact rows; the sums are reduced over
+// the 4 lanes by an xor butterfly (a fixed order, the same result on every
+// lane) and every lane solves the same system. Bound by latency (a chain of
+// some 1500 FP64 and index operations, one or two waves per SIMD on most
+// lattices), so the loads are kept off that chain: the 7 flags of a lane
+// come in at once, the normals and PLIC offsets of row t + LSQR_AHEAD are in
+// flight while row t is added, and a contact row reads its cell's contact
+// data, which store_contact has left there (STORED), instead of computing it
+// from 18 neighbour flags and a chain of square roots and divisions for each
+// of the up to 27 fits that use it. STORED holds while the wall list fits
+// the room for it (a fifth of the cells); otherwise the contact data are
+// computed here, with the same operations. At 2 waves per SIMD it takes 218
+// VGPRs and spills none; held to 3 waves (168 VGPRs) it spilled 35 and took
+// 37 us instead of 25 on the 66,000 interface cells of a sphere of radius
+// 64. Before (loads behind each row's branch, 3 waves): 35 us there, 33 now
+// 27 on the sweep's four LSQR droplets, 27 now 19 on the 256 x 256 x 128
+// sessile drop, 19 now 13 on the 128^3 one (FP32). Rows 3 or 7 ahead: equal.
+constexpr int LSQR_AHEAD = 2;
+
+template <class P, bool STORED>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_curv_lsqr4(const Batch<P> B)
 {
     const Params &prm = B.p[blockIdx.y];
     if (prm.curv != 1) return;
     const Fields<P> &F = B.f[blockIdx.y];
     using R = typename P::R;
     const int n = list_count(F.sc);
+    const int32_t *list = interface_list(F);
+    const size_t N = F.N;
     const int l = threadIdx.x & 3;
+    constexpr int ROWS = 7;
     for (int k = blockIdx.x * 64 + (threadIdx.x >> 2); k < n; k += gridDim.x * 64) {
-        const int i = interface_list(F)[k];
+        const int i = list[k];
         const int yz = i / F.nx, x = i - yz * F.nx, z = yz / F.ny, y = yz - z * F.ny;
-        const LsqrView<P> V{F, x, y, z};
-        LsqrFrame f;
-        V.normal(0, 0, 0, f.nc);
-        f.ok = !(f.nc[0] == 0.0 && f.nc[1] == 0.0 && f.nc[2] == 0.0);
-        // obstacles in the block: each lane scans its share
-        bool ob = false;
+        const R c0 = F.nrm[i], c1 = F.nrm[N + i], c2 = F.nrm[2 * N + i], ca = F.plic[i];
+        const uint8_t fc = F.flags[i];
+        // row t: block cell s = l + 4 t (the centre stands in for s = 27)
+        auto cell = [&](int t) { return l + 4 * t < 27 ? l + 4 * t : 13; };
+        int at[ROWS];
+        uint8_t fl[ROWS];
 #pragma unroll
-        for (int t = 0; t < 7; ++t) {
-            const int s = l + 4 * t;
-            if (s < 27) ob |= (V.flag(s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1) & FL_OBST) != 0;
+        for (int t = 0; t < ROWS; ++t) {
+            const int s = cell(t);
+            at[t] = gidx(x + s % 3 - 1, y + (s / 3) % 3 - 1, z + s / 9 - 1, F.nx, F.ny, F.nz);
+            fl[t] = F.flags[at[t]];
+        }
+        R n0[ROWS], n1[ROWS], n2[ROWS], pa[ROWS];
+        auto load = [&](int t) {
+            n0[t] = F.nrm[at[t]];
+            n1[t] = F.nrm[N + at[t]];
+            n2[t] = F.nrm[2 * N + at[t]];
+            pa[t] = F.plic[at[t]];
+        };
+#pragma unroll
+        for (int t = 0; t < LSQR_AHEAD; ++t) load(t);
+        bool ob = false;
+        unsigned rows = 0;  // bit t: row t has an interface cell other than the centre
+#pragma unroll
+        for (int t = 0; t < ROWS; ++t) {
+            ob |= (fl[t] & FL_OBST) != 0;
+            rows |= cell(t) != 13 && (fl[t] & FL_IF) ? 1u << t : 0u;
         }
         ob |= __shfl_xor(ob ? 1 : 0, 1, 4) != 0;
         ob |= __shfl_xor(ob ? 1 : 0, 2, 4) != 0;
-        lsqr_frame_finish(V, prm, f, ob);
-        LsqrSums S;
-        if (f.ok) {
-#pragma unroll
-            for (int t = 0; t < 7; ++t) {
-                const int s = l + 4 * t;
-                if (s < 27) lsqr_cell_rows(V, prm, f, s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1, S);
+        LsqrFrame f;
+        f.nc[0] = double(c0); f.nc[1] = double(c1); f.nc[2] = double(c2);
+        f.ok = !(f.nc[0] == 0.0 && f.nc[1] == 0.0 && f.nc[2] == 0.0);
+        lsqr_frame_axes(f, double(ca), ob);
+        // the contact condition of block cell j at offset (a, b, c)
+        auto contact = [&](int j, int a, int b, int c, const double(&nj)[3], double aj, double &uc, double &vc, double &ru,
+                           double &rv) {
+            if constexpr (STORED) {
+                const double *d = F.contact + 6 * (size_t)F.wpos[j];
+                const double mh[3] = {d[0], d[1], d[2]}, tg[3] = {d[3], d[4], d[5]};
+                return contact_row(mh, tg, a, b, c, nj, aj, f.pc, f.nc, f.tu, f.tv, uc, vc, ru, rv);
+            } else {
+                const LsqrView<P> V{F, x, y, z};
+                return contact_condition(V, a, b, c, f.pc, f.nc, f.tu, f.tv, prm, uc, vc, ru, rv);
             }
-            if (f.has_obst)
-                for (int t = 0; t < 7; ++t) {
-                    const int s = l + 4 * t;
-                    if (s < 27) lsqr_contact_rows(V, prm, f, s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1, S);
-                }
+        };
+        if (f.ok && ob && (fc & FL_NEAR_OBST)) f.hard = contact(i, 0, 0, 0, f.nc, double(ca), f.huc, f.hvc, f.hu, f.hv);
+        LsqrSums S;
+#pragma unroll
+        for (int t = 0; t < ROWS; ++t) {
+            if (t + LSQR_AHEAD < ROWS) load(t + LSQR_AHEAD);
+            const int s = cell(t), a = s % 3 - 1, b = (s / 3) % 3 - 1, c = s / 9 - 1;
+            const double nj[3] = {double(n0[t]), double(n1[t]), double(n2[t])};
+            if (f.ok && (rows >> t & 1) && !(nj[0] == 0.0 && nj[1] == 0.0 && nj[2] == 0.0))
+                lsqr_data_row(f, a, b, c, nj, double(pa[t]), S);
+            __builtin_amdgcn_sched_barrier(0);  // the loads ahead stay LSQR_AHEAD rows deep
+        }
+        if (f.ok && ob) {
+            for (int t = 0; t < ROWS; ++t) {
+                if (!(rows >> t & 1)) continue;
+                const int s = cell(t), a = s % 3 - 1, b = (s / 3) % 3 - 1, c = s / 9 - 1;
+                const int j = gidx(x + a, y + b, z + c, F.nx, F.ny, F.nz);
+                if (!(F.flags[j] & FL_NEAR_OBST)) continue;
+                const double nj[3] = {double(F.nrm[j]), double(F.nrm[N + j]), double(F.nrm[2 * N + j])};
+                double uc, vc, ru, rv;
+                if (contact(j, a, b, c, nj, double(F.plic[j]), uc, vc, ru, rv)) lsqr_contact_row(f, uc, vc, ru, rv, S);
+            }
         }
 #pragma unroll
         for (int m = 1; m < 4; m <<= 1) {
@@ -1022,9 +1039,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(3))) void k
         if (l == 0) F.K[i] = R(K);
         if (l == 1 && F.snap && k < F.sc->icount) {
             R *sn = F.snap + (size_t)SNAP * k;
-            const size_t N = F.N;
             sn[0] = F.m[i]; sn[1] = F.rho[i]; sn[2] = F.phi[i]; sn[3] = R(K);
-            sn[4] = F.nrm[i]; sn[5] = F.nrm[N + i]; sn[6] = F.nrm[2 * N + i]; sn[7] = F.plic[i];
+            sn[4] = c0; sn[5] = c1; sn[6] = c2; sn[7] = ca;
         }
     }
 }
@@ -1073,7 +1089,7 @@ __global__ __launch_bounds__(256) void k_curv_tr(const Batch<P> B)
         LsqrFrame f;
         V.normal(0, 0, 0, f.nc);
         f.ok = live && !(f.nc[0] == 0.0 && f.nc[1] == 0.0 && f.nc[2] == 0.0);
-        lsqr_frame_finish(V, prm, f, false);
+        lsqr_frame_axes(f, f.ok ? V.plic(0, 0, 0) : 0.0, false);
         // this lane's point
         const int a = s % 3 - 1, b = (s / 3) % 3 - 1, c = s / 9 - 1;
         bool valid = f.ok && s < 27 && s != 13;
