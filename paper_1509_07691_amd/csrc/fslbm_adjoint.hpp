@@ -100,6 +100,25 @@ __global__ void k_adj_zero(double *p, size_t n)
     for (size_t i = blockIdx.x * (size_t)256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = 0.0;
 }
 
+// gin and own of the fluid cells = 0 (own of a liquid cell away from walls is
+// never read; nor is either of another cell).
+template <class P>
+__global__ __launch_bounds__(256) void k_adj_zero_fluid(Fields<P> F, double *gin, double *own)
+{
+    const CellRange box = CellRange::from(F.sc->fbox);
+    const size_t N = F.N;
+    for (long long k = blockIdx.x * 256LL + threadIdx.x; k < box.size(); k += gridDim.x * 256LL) {
+        const int i = box.cell(int(k), F.nx, F.ny);
+        const uint8_t fl = F.flags[i];
+        if (!(fl & FL_FLUID)) continue;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) gin[q * N + i] = 0.0;
+        if (fl == FL_LIQ) continue;
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) own[q * N + i] = 0.0;
+    }
+}
+
 // pos[] of the interface cells and phib = dL/dphi_T there.
 template <class P>
 __global__ void k_adj_begin(Fields<P> F, Adj A, const double *dphi)
