@@ -953,8 +953,10 @@ int enqueue_geometry(const fslbm_batch *b, const Batch<P> &A, int maxN, int eos 
     const hipStream_t st = bstream(b);
     const dim3 tg(std::min(GEOM_GRID, std::max(1, maxN / 512)), n);
     bool any_fd = false, any_fd_wall = false, any_lsqr = false, any_tr = false, stored = true;
+    long long fd_cells = 0;  // interface cells (at creation) of the FD lattices
     for (auto *h : b->hs) {
         if (h->curv == FSLBM_CURV_LSQR) stored &= keeps_contact(h);
+        if (h->curv == FSLBM_CURV_FD) fd_cells += h->icount0;
         any_fd |= h->curv == FSLBM_CURV_FD;
         any_fd_wall |= h->curv == FSLBM_CURV_FD && h->ocount0 > 0;
         any_lsqr |= h->curv == FSLBM_CURV_LSQR;
@@ -968,7 +970,8 @@ int enqueue_geometry(const fslbm_batch *b, const Batch<P> &A, int maxN, int eos 
         eos = 0;
     }
     if (any_fd && any_plic) k_geometry_mixed<P><<<tg, 256, 0, st>>>(A, eos);
-    else if (any_fd) k_geometry_fd<P><<<tg, 256, 0, st>>>(A, eos);
+    else if (any_fd && fd_cells <= FD_FEW_CELLS) k_geometry_fd<P, 512><<<tg, 512, 0, st>>>(A, eos);
+    else if (any_fd) k_geometry_fd<P, 256><<<tg, 256, 0, st>>>(A, eos);
     else k_normals_plic<P><<<dim3(batch_list_blocks(b, 256), n), 256, 0, st>>>(A, eos);
     if (any_lsqr && stored) k_curv_lsqr4<P, true><<<cg4, 256, 0, st>>>(A);
     else if (any_lsqr) k_curv_lsqr4<P, false><<<cg4, 256, 0, st>>>(A);

@@ -195,19 +195,6 @@ __device__ inline int gidx(int x, int y, int z, int nx, int ny, int nz)
     return wrapi(x, nx) + nx * (wrapi(y, ny) + ny * wrapi(z, nz));
 }
 
-// Does the tile hold an interface cell? (uniform across the workgroup)
-template <class P>
-__device__ inline bool tile_has_interface(const Fields<P> &F, const Tiles &T, int ox, int oy, int oz)
-{
-    int has = 0;
-    for (int c = threadIdx.x; c < TILE * TILE * TILE; c += 256) {
-        const int lx = c % TILE, ly = (c / TILE) % TILE, lz = c / (TILE * TILE);
-        if (!T.inside(ox + lx, oy + ly, oz + lz)) continue;
-        has |= F.flags[gidx(ox + lx, oy + ly, oz + lz, F.nx, F.ny, F.nz)] & FL_IF;
-    }
-    return __syncthreads_or(has) != 0;
-}
-
 // Unscaled Parker-Youngs gradient of an LDS cube of edge E at (x, y, z).
 template <int E, class G, class A>
 __device__ inline void py_grad_lds(const A &g, int x, int y, int z, G &gx, G &gy, G &gz)
@@ -256,11 +243,23 @@ __device__ inline double k8w(int r2) { return r2 == 0 ? 256.0 : (r2 == 1 ? 81.0 
 constexpr double K8_INV = 1.0 / 942.0;
 
 
-// FD model, one 8^3 tile per iteration. LDS: the fill level on the tile
-// grown by 3 (14^3), the mollified fill level grown by 2 (12^3) and the
-// mollified unit normals grown by 1 (10^3, reusing the fill-level space).
-// The raw-fill normals of the tile's interface cells (for the corner rule)
-// come from the same LDS copy.
+// FD model, one 8^3 tile per iteration, one thread per tile cell. LDS: the
+// fill level on the tile grown by 3 (14^3), the mollified fill level grown by
+// 2 (12^3) and the mollified unit normals grown by 1 (10^3, reusing the
+// fill-level space). The raw-fill normals of the tile's interface cells (for
+// the corner rule) come from the same LDS copy.
+//
+// On a lattice with few tiles the length of a thread's own chain through the
+// five stages bounds it (one tile per CU), mostly LDS reads. There 512 threads
+// share a tile, and a thread of the two dense stages takes a few cells of a
+// column (CM, CN) and reads the planes they share once: mollification 4 cells
+// from 54 values instead of 108, normals 2 from 36 instead of 108. That takes
+// 116 VGPRs in FP32 (152 in FP64) and half the blocks per CU, so many tiles
+// keep 256 threads with a cell each, where issue bounds it. Measured per
+// launch: 97 x 61 x 83 FP32 13.1 -> 8.6 us, 24^3 and 64^3 FP64 14.2 -> 10.5 us;
+// but the sweep's 1200 tiles (FP32) 32 -> 45 us (36 with a quarter of the
+// blocks). The line lies at FD_FEW_CELLS interface cells, about 64 to a tile:
+// 512 tiles, what the device holds at once in that form.
 template <class G> struct FdLds {
     G buf[3000];  // phi 14^3 (origin -3), later normals 3 x 10^3 (origin -1)
     G mol[1728];  // mollified phi 12^3 (origin -2)
@@ -389,87 +388,125 @@ __global__ __launch_bounds__(256) void k_fd_contact_normals(const Batch<P> B, in
     }
 }
 
-template <class P>
+constexpr int FD_FEW_CELLS = 512 * 64;
+
+template <class P, int NT>
 __device__ inline void geometry_fd_tiles(const Fields<P> &F)
 {
     using R = typename P::R;
     using G = typename P::G;
+    constexpr int CELLS = TILE * TILE * TILE, CM = NT == 512 ? 4 : 1, CN = NT == 512 ? 2 : 1;
     __shared__ FdLds<G> L;
     const Tiles T(F.sc);
-    const int nt = T.count();
+    const int nt = T.count(), tid = threadIdx.x;
+    const bool walls = F.sc->ocount > 0;
     for (int t = blockIdx.x; t < nt; t += gridDim.x) {
         int ox, oy, oz;
         T.origin(t, ox, oy, oz);
-        __syncthreads();
-        if (!tile_has_interface(F, T, ox, oy, oz)) continue;
-        // the fill level on the 14^3 block: thread c < 196 takes column
-        // (x, y) = (c % 14, c / 14) and walks it in z with a running plane
-        // offset (no index division or product per element)
-        if (threadIdx.x < 196) {
-            const int c = threadIdx.x, x = c % 14, y = c / 14;
+        // this thread's interface cells of the tile (-1: none)
+        int ifc[CELLS / NT];
+        bool any = false;
+#pragma unroll
+        for (int m = 0; m < CELLS / NT; ++m) {
+            const int c = tid + m * NT, ux = ox + c % 8, uy = oy + (c / 8) % 8, uz = oz + c / 64;
+            const int i = T.inside(ux, uy, uz) ? gidx(ux, uy, uz, F.nx, F.ny, F.nz) : -1;
+            ifc[m] = i >= 0 && (F.flags[i] & FL_IF) ? i : -1;
+            any |= ifc[m] >= 0;
+        }
+        if (!__syncthreads_or(any)) continue;  // the barrier also frees the last tile's LDS
+        // the fill level on the 14^3 block: a thread takes a part of a column
+        // (x, y), walked in z with a running plane offset (no index division
+        // or product per element)
+        constexpr int ZP = NT == 512 ? 7 : 14;
+        if (tid < 196 * (14 / ZP)) {
+            const int c = tid % 196, z0 = tid / 196 * ZP, x = c % 14, y = c / 14;
             const int col = wrapi(ox - 3 + x, F.nx) + F.nx * wrapi(oy - 3 + y, F.ny);
             const int nxy = F.nx * F.ny;
-            int zoff = wrapi(oz - 3, F.nz) * nxy;
+            int zoff = wrapi(oz - 3 + z0, F.nz) * nxy;
 #pragma unroll
-            for (int z = 0; z < 14; ++z) {
-                L.buf[z * 196 + c] = G(F.phi[col + zoff]);
+            for (int z = 0; z < ZP; ++z) {
+                L.buf[(z0 + z) * 196 + c] = G(F.phi[col + zoff]);
                 zoff += nxy;
                 if (zoff >= F.N) zoff -= F.N;
             }
         }
         __syncthreads();
         // raw-fill normals of the tile's interface cells
-        for (int c = threadIdx.x; c < 512; c += 256) {
-            const int lx = c % 8, ly = (c / 8) % 8, lz = c / 64;
-            if (!T.inside(ox + lx, oy + ly, oz + lz)) continue;
-            const int i = gidx(ox + lx, oy + ly, oz + lz, F.nx, F.ny, F.nz);
-            if (!(F.flags[i] & FL_IF)) continue;
+#pragma unroll
+        for (int m = 0; m < CELLS / NT; ++m) {
+            if (ifc[m] < 0) continue;
+            const int c = tid + m * NT;
             G gx, gy, gz, n[3];
-            py_grad_lds<14>(L.buf, lx + 3, ly + 3, lz + 3, gx, gy, gz);
+            py_grad_lds<14>(L.buf, c % 8 + 3, (c / 8) % 8 + 3, c / 64 + 3, gx, gy, gz);
             unit_normal(gx, gy, gz, n);
-            store_normal(F, i, n, G(0));
+            store_normal(F, ifc[m], n, G(0));
         }
-        // K8 mollification on 12^3
-        for (int c = threadIdx.x; c < 1728; c += 256) {
-            const int x = c % 12, y = (c / 12) % 12, z = c / 144;
-            G s = G(0);
+        // K8 mollification on 12^3, CM cells of a column at a time
+        for (int k = tid; k < 144 * (12 / CM); k += NT) {
+            const int c = k % 144, z0 = k / 144 * CM, x = c % 12, y = c / 12;
+            G v[CM + 2][9];
 #pragma unroll
-            for (int dz = -1; dz <= 1; ++dz)
+            for (int p = 0; p < CM + 2; ++p)
 #pragma unroll
-                for (int dy = -1; dy <= 1; ++dy)
+                for (int e = 0; e < 9; ++e) v[p][e] = L.buf[((z0 + p) * 14 + y + e / 3) * 14 + x + e % 3];
 #pragma unroll
-                    for (int dx = -1; dx <= 1; ++dx)
-                        s += G(k8w(dx * dx + dy * dy + dz * dz)) * L.buf[((z + 1 + dz) * 14 + y + 1 + dy) * 14 + x + 1 + dx];
-            L.mol[c] = s * G(K8_INV);
+            for (int o = 0; o < CM; ++o) {
+                G s = G(0);
+#pragma unroll
+                for (int dz = -1; dz <= 1; ++dz)
+#pragma unroll
+                    for (int dy = -1; dy <= 1; ++dy)
+#pragma unroll
+                        for (int dx = -1; dx <= 1; ++dx)
+                            s += G(k8w(dx * dx + dy * dy + dz * dz)) * v[o + 1 + dz][(dy + 1) * 3 + dx + 1];
+                L.mol[(z0 + o) * 144 + c] = s * G(K8_INV);
+            }
         }
         __syncthreads();
-        // unit normals of the mollified field on 10^3; obstacle cells with a
-        // contact normal (FD wetting) take it instead
-        const bool walls = F.sc->ocount > 0;
-        for (int c = threadIdx.x; c < 1000; c += 256) {
-            const int x = c % 10, y = (c / 10) % 10, z = c / 100;
-            G gx, gy, gz, n[3];
-            py_grad_lds<12>(L.mol, x + 1, y + 1, z + 1, gx, gy, gz);
-            unit_normal(gx, gy, gz, n);
-            if (walls) {
-                const int gi = gidx(ox - 1 + x, oy - 1 + y, oz - 1 + z, F.nx, F.ny, F.nz);
-                if (F.flags[gi] & FL_OBST) {
-                    const size_t N = F.N;
-                    const G c0 = G(F.cnrm[gi]), c1 = G(F.cnrm[N + gi]), c2 = G(F.cnrm[2 * N + gi]);
-                    if (c0 != G(0) || c1 != G(0) || c2 != G(0)) { n[0] = c0; n[1] = c1; n[2] = c2; }
+        // unit normals of the mollified field on 10^3, CN cells of a column at
+        // a time; obstacle cells with a contact normal (FD wetting) take it
+        // instead
+        for (int k = tid; k < 100 * (10 / CN); k += NT) {
+            const int c = k % 100, z0 = k / 100 * CN, x = c % 10, y = c / 10;
+            G v[CN + 2][9];
+#pragma unroll
+            for (int p = 0; p < CN + 2; ++p)
+#pragma unroll
+                for (int e = 0; e < 9; ++e) v[p][e] = L.mol[((z0 + p) * 12 + y + e / 3) * 12 + x + e % 3];
+#pragma unroll
+            for (int o = 0; o < CN; ++o) {
+                auto at = [&](int dx, int dy, int dz) { return v[o + 1 + dz][(dy + 1) * 3 + dx + 1]; };
+                G gx = G(0), gy = G(0), gz = G(0), n[3];
+#pragma unroll
+                for (int a = -1; a <= 1; ++a)
+#pragma unroll
+                    for (int b = -1; b <= 1; ++b) {
+                        const G w = G(pyw(a) * pyw(b));
+                        gx += w * (at(1, a, b) - at(-1, a, b));
+                        gy += w * (at(a, 1, b) - at(a, -1, b));
+                        gz += w * (at(a, b, 1) - at(a, b, -1));
+                    }
+                unit_normal(gx, gy, gz, n);
+                if (walls) {
+                    const int gi = gidx(ox - 1 + x, oy - 1 + y, oz - 1 + z0 + o, F.nx, F.ny, F.nz);
+                    if (F.flags[gi] & FL_OBST) {
+                        const size_t N = F.N;
+                        const G c0 = G(F.cnrm[gi]), c1 = G(F.cnrm[N + gi]), c2 = G(F.cnrm[2 * N + gi]);
+                        if (c0 != G(0) || c1 != G(0) || c2 != G(0)) { n[0] = c0; n[1] = c1; n[2] = c2; }
+                    }
                 }
+                const int j = (z0 + o) * 100 + c;
+                L.buf[j] = n[0];
+                L.buf[1000 + j] = n[1];
+                L.buf[2000 + j] = n[2];
             }
-            L.buf[c] = n[0];
-            L.buf[1000 + c] = n[1];
-            L.buf[2000 + c] = n[2];
         }
         __syncthreads();
         // K = -div(n^), PY-weighted central differences scaled by 1/32
-        for (int c = threadIdx.x; c < 512; c += 256) {
-            const int lx = c % 8, ly = (c / 8) % 8, lz = c / 64;
-            if (!T.inside(ox + lx, oy + ly, oz + lz)) continue;
-            const int i = gidx(ox + lx, oy + ly, oz + lz, F.nx, F.ny, F.nz);
-            if (!(F.flags[i] & FL_IF)) continue;
+#pragma unroll
+        for (int m = 0; m < CELLS / NT; ++m) {
+            if (ifc[m] < 0) continue;
+            const int c = tid + m * NT, lx = c % 8, ly = (c / 8) % 8, lz = c / 64;
             G dxx = 0, dyy = 0, dzz = 0;
             auto at = [&](int comp, int dx, int dy, int dz) {
                 return L.buf[comp * 1000 + ((lz + 1 + dz) * 10 + ly + 1 + dy) * 10 + lx + 1 + dx];
@@ -483,17 +520,17 @@ __device__ inline void geometry_fd_tiles(const Fields<P> &F)
                     dyy += w * (at(1, a, 1, b) - at(1, a, -1, b));
                     dzz += w * (at(2, a, b, 1) - at(2, a, b, -1));
                 }
-            F.K[i] = R(-((dxx + dyy + dzz) / G(32)));
+            F.K[ifc[m]] = R(-((dxx + dyy + dzz) / G(32)));
         }
     }
 }
 
-template <class P>
-__global__ __launch_bounds__(256) void k_geometry_fd(const Batch<P> B, int eos)
+template <class P, int NT>
+__global__ __launch_bounds__(NT) void k_geometry_fd(const Batch<P> B, int eos)
 {
     end_of_step(B.f[blockIdx.y].sc, eos);
     if (B.p[blockIdx.y].curv != 0) return;
-    geometry_fd_tiles(B.f[blockIdx.y]);
+    geometry_fd_tiles<P, NT>(B.f[blockIdx.y]);
 }
 
 // LSQR model: one thread per interface cell over the interface list (the
@@ -919,7 +956,7 @@ template <class P>
 __global__ __launch_bounds__(256) void k_geometry_mixed(const Batch<P> B, int eos)
 {
     end_of_step(B.f[blockIdx.y].sc, eos);
-    if (B.p[blockIdx.y].curv == 0) geometry_fd_tiles(B.f[blockIdx.y]);
+    if (B.p[blockIdx.y].curv == 0) geometry_fd_tiles<P, 256>(B.f[blockIdx.y]);
     else normals_plic_list(B.f[blockIdx.y], B.p[blockIdx.y]);
 }
 
