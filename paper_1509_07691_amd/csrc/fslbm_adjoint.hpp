@@ -433,6 +433,37 @@ __global__ __launch_bounds__(256) void k_adj_stream(const Fields<P> F, const Adj
     }
 }
 
+// The interface box grown by g cells on every side (periodic; an axis that
+// would overlap itself is taken whole). Outside it the adjoints of the FD
+// chain are zero: kbar is not zero only at interface cells, and each stencil,
+// the contact normal's step to its base cell among them, reaches one or two
+// cells further. The buffers start at zero, and the box of a frozen window
+// does not move.
+struct GrownBox {
+    CellRange r;
+    int nx, ny, nz;
+    template <class P>
+    __device__ inline GrownBox(const Fields<P> &F, int g) : r(CellRange::from(F.sc->bbox)), nx(F.nx), ny(F.ny), nz(F.nz)
+    {
+        if (r.size() == 0) return;
+        grow(r.x0, r.ex, nx, g);
+        grow(r.y0, r.ey, ny, g);
+        grow(r.z0, r.ez, nz, g);
+    }
+    __device__ static inline void grow(int &o, int &e, int n, int g)
+    {
+        o = e + 2 * g < n ? o - g : 0;
+        e = min(e + 2 * g, n);
+    }
+    __device__ inline Nbr at(int k) const
+    {
+        const unsigned uk = unsigned(k), row = uk / unsigned(r.ex);
+        return Nbr(wrapi(r.x0 + int(uk - row * unsigned(r.ex)), nx), wrapi(r.y0 + int(row % unsigned(r.ey)), ny),
+                   wrapi(r.z0 + int(row / unsigned(r.ey)), nz), nx, ny, nz);
+    }
+};
+constexpr int FD_GROW = 5;  // gb reaches 3 cells from the interface (a contact normal's base cell), msb 4, phib 5
+
 // ------------------------------------------------ FD curvature (reverse)
 // Forward (Sec. II.A): ms = K8 * phi / 942, g = PY(ms), n = g/|g|,
 // K = -(PY_x n_x + PY_y n_y + PY_z n_z)/32 at interface cells. Each PY
@@ -441,8 +472,10 @@ __global__ __launch_bounds__(256) void k_adj_stream(const Fields<P> F, const Adj
 template <class P>
 __global__ __launch_bounds__(256) void k_adj_fd_mol(const Fields<P> F, const Adj A)
 {
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < F.N; i += gridDim.x * 256) {
-        const Nbr nb(i, F.nx, F.ny, F.nz);
+    const GrownBox box(F, FD_GROW);
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < box.r.size(); k += gridDim.x * 256) {
+        const Nbr nb = box.at(k);
+        const int i = nb.at(0, 0, 0);
         double s = 0.0;
 #pragma unroll
         for (int c = -1; c <= 1; ++c)
@@ -531,8 +564,10 @@ __global__ __launch_bounds__(256) void k_adj_fd_nbar(const Fields<P> F, const Ad
 {
     const size_t N = F.N;
     const bool walls = F.sc->ocount > 0;
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < F.N; i += gridDim.x * 256) {
-        const Nbr nb(i, F.nx, F.ny, F.nz);
+    const GrownBox box(F, FD_GROW);
+    for (int c = blockIdx.x * 256 + threadIdx.x; c < box.r.size(); c += gridDim.x * 256) {
+        const Nbr nb = box.at(c);
+        const int i = nb.at(0, 0, 0);
         const uint8_t fl = F.flags[i];
         double b[3];
         py_grad(A.kbar, nb, b[0], b[1], b[2]);
@@ -603,8 +638,10 @@ __device__ inline double py_div_t(const double *gb, size_t N, const Nbr &nb)
 template <class P>
 __global__ __launch_bounds__(256) void k_adj_fd_msb(const Fields<P> F, const Adj A)
 {
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < F.N; i += gridDim.x * 256) {
-        const Nbr nb(i, F.nx, F.ny, F.nz);
+    const GrownBox box(F, FD_GROW);
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < box.r.size(); k += gridDim.x * 256) {
+        const Nbr nb = box.at(k);
+        const int i = nb.at(0, 0, 0);
         A.msb[i] = py_div_t(A.gb, F.N, nb);
     }
 }
@@ -614,10 +651,12 @@ __global__ __launch_bounds__(256) void k_adj_fd_msb(const Fields<P> F, const Adj
 template <class P>
 __global__ __launch_bounds__(256) void k_adj_fd_phib(const Fields<P> F, const Adj A)
 {
-    for (int i = blockIdx.x * 256 + threadIdx.x; i < F.N; i += gridDim.x * 256) {
+    const GrownBox box(F, FD_GROW);
+    for (int k = blockIdx.x * 256 + threadIdx.x; k < box.r.size(); k += gridDim.x * 256) {
+        const Nbr nb = box.at(k);
+        const int i = nb.at(0, 0, 0);
         const uint8_t fl = F.flags[i];
         if (!(fl & (FL_IF | FL_OBST))) continue;
-        const Nbr nb(i, F.nx, F.ny, F.nz);
         double s = 0.0;
 #pragma unroll
         for (int c = -1; c <= 1; ++c)
@@ -767,24 +806,21 @@ __host__ __device__ inline void plic_derivs(const double (&n)[3], double phi, do
 // contact_condition and its reverse in one pass: the forward values
 // (u_c, v_c, -m_u/m_n, -m_v/m_n) go to seeds(uc, vc, ru, rv, ucb, vcb, rub,
 // rvb), which returns their adjoints; from those the adjoints of p_c, n_c,
-// t_u, t_v, of the contact cell's normal and PLIC offset (into its slot of
-// cb) and of theta are accumulated. Nothing happens (seeds is not called)
+// t_u, t_v, of the contact cell's normal and PLIC offset (c[0..2], c[3])
+// and of theta are accumulated. Nothing happens (seeds is not called)
 // where contact_condition skips the condition.
 template <class View, class Seeds>
 __host__ __device__ inline void contact_condition_adj(const View &V, int dx, int dy, int dz, const double (&pc)[3],
                                                       const double (&nc)[3], const double (&tu)[3],
                                                       const double (&tv)[3], const Params &prm, Seeds &&seeds,
                                                       double (&pcb)[3], double (&ncb)[3], double (&tub)[3],
-                                                      double (&tvb)[3], double *cb, double &thb)
+                                                      double (&tvb)[3], double (&c)[4], double &thb)
 {
     double nj[3];
     V.normal(dx, dy, dz, nj);
     if (nj[0] == 0.0 && nj[1] == 0.0 && nj[2] == 0.0) return;
-    int sx = 0, sy = 0, sz = 0;
-    for (int q = 1; q < NQ; ++q)
-        if (V.flag(dx + dir_x(q), dy + dir_y(q), dz + dir_z(q)) & FL_OBST) {
-            sx += dir_x(q); sy += dir_y(q); sz += dir_z(q);
-        }
+    int sx, sy, sz;
+    V.wall_dir(dx, dy, dz, sx, sy, sz);
     const double lw = sqrt(double(sx * sx + sy * sy + sz * sz));
     if (!(lw > 0.0)) return;
     const double nw[3] = {sx / lw, sy / lw, sz / lw};
@@ -840,7 +876,6 @@ __host__ __device__ inline void contact_condition_adj(const View &V, int dx, int
         nnb -= ntrb * nw[k];
     }
     for (int k = 0; k < 3; ++k) njb[k] += nnb * nw[k];
-    double *c = cb + 4 * slot27(dx, dy, dz);
     c[0] += njb[0];
     c[1] += njb[1];
     c[2] += njb[2];
@@ -867,22 +902,35 @@ __host__ __device__ inline int group_sum_int(int v)
     return v;
 }
 
-// Reverse of the LSQR curvature for dL/dK = Kb, by the L lanes of a group
-// (lane = 0..L-1; L = 1 is the plain serial form). The forward fit is
-// recomputed (same rows and model choice as lsqr_curvature, sums reduced
-// over the lanes): the frame, the centre's hard constraint, the normal
-// equations, their solution x and y = G^-1 xbar are the same on every lane.
-// Lane l owns the block cells s = l, l + L, ... (s = slot27): it forms
-// their rows' adjoints (bbar = m.y, mbar = r y - (m.y) x per row) and
-// writes dL/dn_s, dL/da_s into cb[4 s + 0..3]. The adjoints of the shared
-// quantities (centre point, frame, hard-constraint values, theta) are
-// reduced over the lanes; lane 0 then reverses the centre's hard
-// constraint and the frame into slot 13 and returns dL/dtheta in thb (the
-// other lanes return 0).
-template <int L, class View>
-__host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &prm, double Kb, int lane, double *cb,
-                                                   double &thb)
+// Per interface cell, 16 lanes (measured faster than 8: the block cells'
+// rows and contact conditions spread over more lanes shorten the chain of
+// the wall cells, which sets the kernel's time).
+constexpr int ADJ_LANES = 16;
+
+// Reverse of the LSQR curvature for dL/dK = Kb, by the ADJ_LANES lanes of a
+// group (lane = 0..ADJ_LANES-1). The forward fit is recomputed (same rows
+// and model choice as k_curv_lsqr4, sums reduced over the lanes): the frame,
+// the centre's hard constraint, the normal equations, their factor, solution
+// x and y = G^-1 xbar are the same on every lane. Lane l owns the block cells
+// s = l + ADJ_LANES u (s = slot27): it forms their rows' adjoints (bbar =
+// m.y, mbar = r y - (m.y) x per row) and adds dL/dn_s, dL/da_s to cb[u]. The
+// adjoints of the shared quantities (centre point, frame, hard-constraint
+// values, theta) are reduced over the lanes; lane 0 then reverses the
+// centre's hard constraint and the frame into cc (the centre's own partials)
+// and returns dL/dtheta in thb (the other lanes return 0).
+//
+// Bound by one lane's chain of FP64 operations (440 blocks for 7000 cells).
+// The partials stay in registers until the end, the factor is taken once for
+// both solves, a contact cell's wall direction comes from the static table
+// instead of 18 flags, and the two cells of a lane share one copy of the long
+// row bodies (unrolled they spilled 172 VGPRs and took 35 us): 33 -> 27 us per
+// launch on the 128^3 sessile drop.
+constexpr int ADJ_OWN = (27 + ADJ_LANES - 1) / ADJ_LANES;
+template <class View>
+__device__ inline void lsqr_curvature_adj(const View &V, const Params &prm, double Kb, int lane, double (&cb)[ADJ_OWN][4],
+                                          double (&cc)[4], double &thb)
 {
+    constexpr int L = ADJ_LANES;
     thb = 0.0;
     double nc[3];
     V.normal(0, 0, 0, nc);
@@ -899,7 +947,11 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
     const double ac = V.plic(0, 0, 0);
     const double pc[3] = {ac * nc[0], ac * nc[1], ac * nc[2]};
     int ob = 0;
-    for (int s = lane; s < 27; s += L) ob |= (V.flag(s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1) & FL_OBST) != 0;
+#pragma unroll
+    for (int u = 0; u < ADJ_OWN; ++u) {
+        const int s = lane + L * u;
+        if (s < 27) ob |= (V.flag(s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1) & FL_OBST) != 0;
+    }
     const bool has_obst = group_sum_int<L>(ob) != 0;
     LsqrFrame fr;
     for (int k = 0; k < 3; ++k) {
@@ -919,7 +971,11 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
 
     // ---- forward fit, rows split over the lanes
     LsqrSums S;
-    for (int s = lane; s < 27; s += L) lsqr_cell_rows(V, fr, s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1, S);
+#pragma unroll
+    for (int u = 0; u < ADJ_OWN; ++u) {
+        const int s = lane + L * u;
+        if (s < 27) lsqr_cell_rows(V, fr, s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1, S);
+    }
     if (has_obst)
         for (int s = lane; s < 27; s += L) lsqr_contact_rows(V, prm, fr, s % 3 - 1, (s / 3) % 3 - 1, s / 9 - 1, S);
     for (int e = 0; e < 15; ++e) S.G[e] = group_sum<L>(S.G[e]);
@@ -929,21 +985,23 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
     // (the same choice as lsqr_solve_curvature)
     int model = 0;
     double x[5] = {0, 0, 0, 0, 0};
-    double Gm[15];
+    double Lf[15];  // the factor of the chosen model's system
     double A = 0, Bq = 0, C = 0, H = 0, I = 0;
     const double *G = S.G, *g = S.g;
     const double G3i[6] = {G[0] + 2.0 * G[1] + G[2], G[6] + G[7], G[9], G[10] + G[11], G[13], G[14]};
     const double G1[1] = {G[0] + 2.0 * G[1] + G[2]};
     if (!hard) {
         double x5[5];
-        if (S.rows >= 5 && packed_solve<5>(G, g, x5)) {
+        if (S.rows >= 5 && packed_factor<5>(G, Lf)) {
+            packed_back<5>(Lf, g, x5);
             model = 1;
             for (int k = 0; k < 5; ++k) x[k] = x5[k];
             A = x5[0]; Bq = x5[1]; C = x5[2]; H = x5[3]; I = x5[4];
         } else if (S.rows >= 3) {
             const double g3[3] = {g[0] + g[1], g[3], g[4]};
             double x3[3];
-            if (packed_solve<3>(G3i, g3, x3)) {
+            if (packed_factor<3>(G3i, Lf)) {
+                packed_back<3>(Lf, g3, x3);
                 model = 2;
                 x[0] = x3[0]; x[1] = x3[1]; x[2] = x3[2];
                 A = x3[0]; Bq = x3[0]; C = 0.0; H = x3[1]; I = x3[2];
@@ -951,14 +1009,16 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
         }
     } else {
         double x3[3];
-        if (S.rows >= 3 && packed_solve<3>(G, g, x3)) {
+        if (S.rows >= 3 && packed_factor<3>(G, Lf)) {
+            packed_back<3>(Lf, g, x3);
             model = 3;
             x[0] = x3[0]; x[1] = x3[1]; x[2] = x3[2];
             A = x3[0]; Bq = x3[1]; C = x3[2];
         } else if (S.rows >= 1) {
             const double g1[1] = {g[0] + g[1]};
             double x1[1];
-            if (packed_solve<1>(G1, g1, x1)) {
+            if (packed_factor<1>(G1, Lf)) {
+                packed_back<1>(Lf, g1, x1);
                 model = 4;
                 x[0] = x1[0];
                 A = x1[0]; Bq = x1[0]; C = 0.0;
@@ -994,17 +1054,17 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
     if (model == 1) {
         const double xb[5] = {Ab, Bb, Cb, Hb, Ib};
         double yy[5];
-        packed_solve<5>(G, xb, yy);
+        packed_back<5>(Lf, xb, yy);
         for (int k = 0; k < 5; ++k) y[k] = yy[k];
     } else if (model == 2 || model == 3) {
         const double xb[3] = {model == 2 ? Ab + Bb : Ab, model == 2 ? Hb : Bb, model == 2 ? Ib : Cb};
         double yy[3];
-        packed_solve<3>(model == 2 ? G3i : G, xb, yy);
+        packed_back<3>(Lf, xb, yy);
         for (int k = 0; k < 3; ++k) y[k] = yy[k];
     } else {
         const double xb[1] = {Ab + Bb};
         double yy[1];
-        packed_solve<1>(G1, xb, yy);
+        packed_back<1>(Lf, xb, yy);
         y[0] = yy[0];
     }
     // per-row adjoints; the hard-constraint adjoints they produce are summed
@@ -1066,9 +1126,11 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
     double pcb[3] = {0, 0, 0}, ncb[3] = {0, 0, 0}, tub[3] = {0, 0, 0}, tvb[3] = {0, 0, 0};
     double thl = 0.0;
     // ---- data rows of this lane's block cells
-    for (int s = lane; s < 27; s += L) {
+#pragma unroll 1
+    for (int m = 0; m < ADJ_OWN; ++m) {
+        const int s = lane + L * m;
+        if (s >= 27 || s == 13) continue;
         const int a = s % 3 - 1, b = (s / 3) % 3 - 1, c = s / 9 - 1;
-        if (a == 0 && b == 0 && c == 0) continue;
         if (!(V.flag(a, b, c) & FL_IF)) continue;
         double nj[3];
         V.normal(a, b, c, nj);
@@ -1089,17 +1151,20 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
             ncb[k] += bb * r[k];
             pcb[k] -= rr[k];
         }
-        double *cs = cb + 4 * s;
-        cs[0] += aj * rr[0];
-        cs[1] += aj * rr[1];
-        cs[2] += aj * rr[2];
-        cs[3] += dot(nj, rr);
+        const double cr[4] = {aj * rr[0], aj * rr[1], aj * rr[2], dot(nj, rr)};
+        for (int e = 0; e < 4; ++e) {
+            cb[0][e] += m == 0 ? cr[e] : 0.0;
+            cb[1][e] += m == 1 ? cr[e] : 0.0;
+        }
     }
     // ---- contact rows of this lane's contact-line cells
     if (has_obst) {
-        for (int s = lane; s < 27; s += L) {
+#pragma unroll 1
+        for (int u = 0; u < ADJ_OWN; ++u) {
+            const int s = lane + L * u;
+            if (s >= 27 || s == 13) continue;
             const int a = s % 3 - 1, b = (s / 3) % 3 - 1, c = s / 9 - 1;
-            if (a == 0 && b == 0 && c == 0) continue;
+            double cr[4] = {};
             const uint8_t fj = V.flag(a, b, c);
             if (!((fj & FL_IF) && (fj & FL_NEAR_OBST))) continue;
             // the two gradient rows of the cell and their adjoints
@@ -1113,7 +1178,11 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
                 ucb = 2.0 * p5[0] + q5[2];
                 vcb = p5[2] + 2.0 * q5[1];
             };
-            contact_condition_adj(V, a, b, c, pc, nc, tu, tv, prm, seeds, pcb, ncb, tub, tvb, cb, thl);
+            contact_condition_adj(V, a, b, c, pc, nc, tu, tv, prm, seeds, pcb, ncb, tub, tvb, cr, thl);
+            for (int e = 0; e < 4; ++e) {
+                cb[0][e] += u == 0 ? cr[e] : 0.0;
+                cb[1][e] += u == 1 ? cr[e] : 0.0;
+            }
         }
     }
     // ---- shared adjoints summed over the lanes
@@ -1138,7 +1207,7 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
             rub = hub;
             rvb = hvb;
         };
-        contact_condition_adj(V, 0, 0, 0, pc, nc, tu, tv, prm, seeds, pcb, ncb, tub, tvb, cb, thb);
+        contact_condition_adj(V, 0, 0, 0, pc, nc, tu, tv, prm, seeds, pcb, ncb, tub, tvb, cc, thb);
     }
     // ---- frame: t_v = n x t_u, t_u = w/|w|, w = e_ax - n_ax n; p_c = a_c n
     ncb[0] += tu[1] * tvb[2] - tu[2] * tvb[1];
@@ -1157,20 +1226,16 @@ __host__ __device__ inline void lsqr_curvature_adj(const View &V, const Params &
     ncb[2] += ax == 2 ? -wn : 0.0;
     const double acb = dot(pcb, nc);
     for (int k = 0; k < 3; ++k) ncb[k] += ac * pcb[k];
-    double *c0 = cb + 4 * slot27(0, 0, 0);
-    c0[0] += ncb[0];
-    c0[1] += ncb[1];
-    c0[2] += ncb[2];
-    c0[3] += acb;
+    cc[0] += ncb[0];
+    cc[1] += ncb[1];
+    cc[2] += ncb[2];
+    cc[3] += acb;
 }
 
-// Per interface cell, 16 lanes (measured faster than 8: the block cells'
-// rows and contact conditions spread over more lanes shorten the chain of
-// the wall cells, which sets the kernel's time): partials of K w.r.t. the
-// normals and PLIC offsets of its block, scaled by dL/dK, into contrib;
+// The reverse fit of every interface cell: partials of K w.r.t. the normals
+// and PLIC offsets of its block, scaled by dL/dK, into contrib (each slot
+// written once, by the lane that owns it; slot 13, the centre, by lane 0);
 // dL/dtheta into tacc.
-constexpr int ADJ_LANES = 16;
-
 template <class P>
 __device__ inline void plic_derivs_blocks(const Fields<P> &F, const Adj &A, int b, int nb);
 
@@ -1198,21 +1263,29 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         const int yz = i / F.nx, x = i - yz * F.nx, z = yz / F.ny, y = yz - z * F.ny;
         double kb = 0.0;
         if (on) {
-            double *cb = A.contrib + (size_t)CONTRIB * k;
-            // each slot is written only by the lane that owns it (slot 13,
-            // the centre, by lane 0), and cleared by that lane
-            for (int s = lane; s < 27; s += ADJ_LANES)
-                if (s != 13) cb[4 * s] = cb[4 * s + 1] = cb[4 * s + 2] = cb[4 * s + 3] = 0.0;
-            if (lane == 0) cb[52] = cb[53] = cb[54] = cb[55] = 0.0;
             kb = A.kbar[i];  // the same for the whole group
-            if (kb != 0.0) lsqr_stage(F, x, y, z, lane, ADJ_LANES, stage[cl]);
+            lsqr_stage(F, x, y, z, lane, ADJ_LANES, stage[cl]);
         }
         __syncthreads();
-        if (on && kb != 0.0) {
-            const LsqrLdsView<typename P::R> V{stage[cl]};
-            double thb = 0.0;
-            lsqr_curvature_adj<ADJ_LANES>(V, prm, kb, lane, A.contrib + (size_t)CONTRIB * k, thb);
-            if (lane == 0) A.tacc[i] += thb;
+        if (on) {
+            double cb[ADJ_OWN][4] = {}, cc[4] = {};
+            if (kb != 0.0) {
+                const LsqrLdsView<typename P::R> V{stage[cl]};
+                double thb = 0.0;
+                lsqr_curvature_adj(V, prm, kb, lane, cb, cc, thb);
+                if (lane == 0) A.tacc[i] += thb;
+            }
+            double *out = A.contrib + (size_t)CONTRIB * k;
+#pragma unroll
+            for (int u = 0; u < ADJ_OWN; ++u) {
+                const int s = lane + ADJ_LANES * u;
+                if (s < 27 && s != 13)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) out[4 * s + e] = cb[u][e];
+            }
+            if (lane == 0)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) out[4 * 13 + e] = cc[e];
         }
         __syncthreads();
     }
@@ -1304,9 +1377,14 @@ template <class P>
 __global__ __launch_bounds__(256) void k_adj_lsqr_phib(const Fields<P> F, const Adj A)
 {
     const int n = F.sc->icount, no = F.sc->ocount;
+    const GrownBox box(F, 2);  // gb is not zero at interface cells only
+    auto off = [](int v, int o, int n) { return v < o ? v - o + n : v - o; };
     for (int k = blockIdx.x * 256 + threadIdx.x; k < n + no; k += gridDim.x * 256) {
         const int i = k < n ? interface_list(F)[k] : F.olist[k - n];
         const Nbr nb(i, F.nx, F.ny, F.nz);
+        if (off(nb.x, box.r.x0, F.nx) >= box.r.ex || off(nb.y, box.r.y0, F.ny) >= box.r.ey ||
+            off(nb.z, box.r.z0, F.nz) >= box.r.ez)
+            continue;
         const double v = py_div_t(A.gb, F.N, nb);
         if (k < n) A.phib[i] += v;
         else A.phib[i] = v;

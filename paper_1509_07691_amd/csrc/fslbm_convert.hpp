@@ -437,9 +437,11 @@ __global__ __launch_bounds__(256) void k_conv_gather(const Batch<P> B)
             const R ph = F.m[i] / F.rho[i];
             F.phi[i] = ph;
             // a frozen window stays on one smooth piece of the step only while
-            // every interface fill lies strictly inside (0, 1)
-            if (frozen && !(ph > R(0) && ph < R(1))) {
-                atomicAdd(&F.sc->fill_out, 1);
+            // every interface fill lies strictly inside (0, 1); one pair of
+            // atomics per wavefront, for most windows have such cells
+            const unsigned long long out = __ballot(frozen && !(ph > R(0) && ph < R(1)));
+            if (out && (threadIdx.x & 63) == (unsigned)(__ffsll(out) - 1)) {
+                atomicAdd(&F.sc->fill_out, __popcll(out));
                 atomicMin(&F.sc->fill_out_step, F.sc->step);
             }
         }

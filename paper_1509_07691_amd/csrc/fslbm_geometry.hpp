@@ -533,6 +533,16 @@ __global__ __launch_bounds__(NT) void k_geometry_fd(const Batch<P> B, int eos)
     geometry_fd_tiles<P, NT>(B.f[blockIdx.y]);
 }
 
+// The directions to the obstacle neighbours of a wall-list cell, summed
+// (static), packed in one word.
+__host__ __device__ inline int pack_dir(int sx, int sy, int sz) { return (sx + 32) | (sy + 32) << 8 | (sz + 32) << 16; }
+__host__ __device__ inline void unpack_dir(int p, int &sx, int &sy, int &sz)
+{
+    sx = (p & 255) - 32;
+    sy = (p >> 8 & 255) - 32;
+    sz = (p >> 16 & 255) - 32;
+}
+
 // LSQR model: one thread per interface cell over the interface list (the
 // fit is FP64 arithmetic with long dependency chains, so full wavefronts
 // matter more than load coalescing). Neighbour data are read through a view
@@ -552,21 +562,36 @@ template <class P> struct LsqrView {
         n[2] = double(F.nrm[2 * N + j]);
     }
     __device__ inline double plic(int dx, int dy, int dz) const { return double(F.plic[at(dx, dy, dz)]); }
+    // the sum of the directions to the obstacle neighbours of a block cell
+    __device__ inline void wall_dir(int dx, int dy, int dz, int &sx, int &sy, int &sz) const
+    {
+        sx = sy = sz = 0;
+#pragma unroll
+        for (int q = 1; q < NQ; ++q)
+            if (flag(dx + dir_x(q), dy + dir_y(q), dz + dir_z(q)) & FL_OBST) {
+                sx += dir_x(q); sy += dir_y(q); sz += dir_z(q);
+            }
+    }
 };
 
 // The same view served from LDS: the lanes that share a centre first copy
-// the flags of its 5 x 5 x 5 block and the normals and PLIC offsets of its
-// 3 x 3 x 3 block (all that the fit and the contact conditions read), as
-// independent loads, so the fit's scattered reads wait for memory once
-// instead of once per dependent access.
+// the flags, normals and PLIC offsets of its 3 x 3 x 3 block and the wall
+// directions of the contact-line cells in it (all that the fit and the
+// contact conditions read), as independent loads, so the fit's scattered
+// reads wait for memory once instead of once per dependent access.
 template <class R> struct LsqrStage {
-    uint8_t fl[128];  // 125 used: (dz + 2) 25 + (dy + 2) 5 + dx + 2
-    R nrm[81];        // 3 per block cell (dz + 1) 9 + (dy + 1) 3 + dx + 1
+    int dir[27];  // pack_dir, at contact-line cells; block cell (dz + 1) 9 + (dy + 1) 3 + dx + 1
+    R nrm[81];    // 3 per block cell
     R pl[27];
+    uint8_t fl[28];
 };
 template <class R> struct LsqrLdsView {
     const LsqrStage<R> &s;
-    __device__ inline uint8_t flag(int dx, int dy, int dz) const { return s.fl[(dz + 2) * 25 + (dy + 2) * 5 + dx + 2]; }
+    __device__ inline uint8_t flag(int dx, int dy, int dz) const { return s.fl[(dz + 1) * 9 + (dy + 1) * 3 + dx + 1]; }
+    __device__ inline void wall_dir(int dx, int dy, int dz, int &sx, int &sy, int &sz) const
+    {
+        unpack_dir(s.dir[(dz + 1) * 9 + (dy + 1) * 3 + dx + 1], sx, sy, sz);
+    }
     __device__ inline void normal(int dx, int dy, int dz, double (&n)[3]) const
     {
         const int j = 3 * ((dz + 1) * 9 + (dy + 1) * 3 + dx + 1);
@@ -581,15 +606,26 @@ template <class P>
 __device__ inline void lsqr_stage(const Fields<P> &F, int x, int y, int z, int lane, int L,
                                   LsqrStage<typename P::R> &s)
 {
-    for (int t = lane; t < 125; t += L)
-        s.fl[t] = F.flags[gidx(x + t % 5 - 2, y + (t / 5) % 5 - 2, z + t / 25 - 2, F.nx, F.ny, F.nz)];
     const size_t N = F.N;
     for (int t = lane; t < 27; t += L) {
-        const int j = gidx(x + t % 3 - 1, y + (t / 3) % 3 - 1, z + t / 9 - 1, F.nx, F.ny, F.nz);
+        const int a = t % 3 - 1, b = (t / 3) % 3 - 1, c = t / 9 - 1;
+        const int j = gidx(x + a, y + b, z + c, F.nx, F.ny, F.nz);
+        const uint8_t fl = F.flags[j];
+        s.fl[t] = fl;
         s.nrm[3 * t] = F.nrm[j];
         s.nrm[3 * t + 1] = F.nrm[N + j];
         s.nrm[3 * t + 2] = F.nrm[2 * N + j];
         s.pl[t] = F.plic[j];
+        if ((fl & FL_IF) && (fl & FL_NEAR_OBST)) {
+            if (F.contact) {
+                s.dir[t] = F.wdir[F.wpos[j]];
+            } else {
+                int sx, sy, sz;
+                const LsqrView<P> V{F, x, y, z};
+                V.wall_dir(a, b, c, sx, sy, sz);
+                s.dir[t] = pack_dir(sx, sy, sz);
+            }
+        }
     }
 }
 
@@ -651,26 +687,13 @@ __host__ __device__ __forceinline__ bool contact_condition(const View &V, int dx
 {
     double nj[3], mh[3], tg[3];
     V.normal(dx, dy, dz, nj);
-    int sx = 0, sy = 0, sz = 0;
-#pragma unroll
-    for (int q = 1; q < NQ; ++q)
-        if (V.flag(dx + dir_x(q), dy + dir_y(q), dz + dir_z(q)) & FL_OBST) {
-            sx += dir_x(q); sy += dir_y(q); sz += dir_z(q);
-        }
+    int sx, sy, sz;
+    V.wall_dir(dx, dy, dz, sx, sy, sz);
     const double aj = V.plic(dx, dy, dz);
     contact_point(nj, aj, sx, sy, sz, prm, mh, tg);
     return contact_row(mh, tg, dx, dy, dz, nj, aj, pc, nc, tu, tv, uc, vc, ru, rv);
 }
 
-// The directions to the obstacle neighbours of a wall-list cell, summed
-// (static), packed in one word.
-__host__ __device__ inline int pack_dir(int sx, int sy, int sz) { return (sx + 32) | (sy + 32) << 8 | (sz + 32) << 16; }
-__host__ __device__ inline void unpack_dir(int p, int &sx, int &sy, int &sz)
-{
-    sx = (p & 255) - 32;
-    sy = (p >> 8 & 255) - 32;
-    sz = (p >> 16 & 255) - 32;
-}
 // Position of each wall-list cell in the list, and its direction sum.
 __global__ __launch_bounds__(256) void k_wall_index(const uint8_t *flags, const int32_t *wlist, int32_t *wpos, int32_t *wdir,
                                                     int cap, const DevScalars *sc, int nx, int ny, int nz)
@@ -742,17 +765,16 @@ __host__ __device__ __forceinline__ void lsqr_frame_axes(LsqrFrame &f, double ac
     f.pc[0] = ac * nc[0]; f.pc[1] = ac * nc[1]; f.pc[2] = ac * nc[2];
 }
 
-// Cholesky solve of a C x C system held as a packed lower triangle
+// Cholesky factor of a C x C system held as a packed lower triangle
 // (entry (r, c), c <= r, at r (r + 1) / 2 + c); fails when a pivot falls
 // below 1e-12 * trace (rank deficiency of the row matrix).
 template <int C>
-__host__ __device__ __forceinline__ bool packed_solve(const double *G, const double *g, double (&x)[C])
+__host__ __device__ __forceinline__ bool packed_factor(const double *G, double *L)
 {
     double tr = 0.0;
 #pragma unroll
     for (int r = 0; r < C; ++r) tr += G[r * (r + 1) / 2 + r];
     if (!(tr > 0.0)) return false;
-    double L[C * (C + 1) / 2];
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         double d = G[c * (c + 1) / 2 + c];
@@ -768,6 +790,12 @@ __host__ __device__ __forceinline__ bool packed_solve(const double *G, const dou
             L[r * (r + 1) / 2 + c] = s / L[c * (c + 1) / 2 + c];
         }
     }
+    return true;
+}
+// The solution for a factor and a right-hand side.
+template <int C>
+__host__ __device__ __forceinline__ void packed_back(const double *L, const double *g, double *x)
+{
     double y[C];
 #pragma unroll
     for (int r = 0; r < C; ++r) {
@@ -783,6 +811,13 @@ __host__ __device__ __forceinline__ bool packed_solve(const double *G, const dou
         for (int j = r + 1; j < C; ++j) s -= L[j * (j + 1) / 2 + r] * x[j];
         x[r] = s / L[r * (r + 1) / 2 + r];
     }
+}
+template <int C>
+__host__ __device__ __forceinline__ bool packed_solve(const double *G, const double *g, double (&x)[C])
+{
+    double L[C * (C + 1) / 2];
+    if (!packed_factor<C>(G, L)) return false;
+    packed_back<C>(L, g, x);
     return true;
 }
 
