@@ -331,6 +331,7 @@ __global__ void k_init_scalars(DevScalars *sc)
     sc->conv_out_step = 0xffffffffu;
     sc->lsel = 0;
     sc->done = 0;
+    sc->vdone = 0;
     for (int k = 0; k < 6; ++k) sc->bbox[k] = 0;
     sc->fbox[0] = sc->fbox[1] = sc->fbox[2] = 1 << 30;
     sc->fbox[3] = sc->fbox[4] = sc->fbox[5] = -1;
@@ -1052,23 +1053,33 @@ int enqueue_step_kernels(fslbm_batch *b, const void *fsrc = nullptr, void *fdst 
     bool frozen = true;
     for (auto *h : b->hs) frozen &= h->frozen != 0;
     mark(b, 2);
-    if (!frozen) k_conv_mark<P><<<vg, 256, 0, st>>>(A);
-    if (!frozen) k_conv_close<P><<<vg, 256, 0, st>>>(A);
-    k_conv_gather<P><<<lg, 256, 0, st>>>(A);
+    // the obstacle fill is grid-stride over the static obstacle list (none
+    // without walls); it shares a launch with phi = m / rho in a frozen step,
+    // else with the bubble's volume sum where there is one
+    int maxo = 0, maxi = 0;
+    bool any_bubble = false;
+    for (auto *h : b->hs) {
+        maxo = std::max(maxo, h->ocount0);
+        maxi = std::max(maxi, h->icount0);
+        any_bubble |= h->bubble != 0;
+    }
+    const int ob = maxo > 0 ? std::min(list_blocks(maxN), (maxo + 255) / 256) : 0;
+    const bool walls_with_phi = frozen && ob > 0 && !any_bubble;
+    if (walls_with_phi) {
+        k_gather_walls<P><<<dim3(lg.x + ob, n), 256, 0, st>>>(A, (int)lg.x);
+    } else if (!frozen && maxi <= CONV_BLOCK_CELLS) {
+        k_conv_block<P><<<dim3(1, n), CONV_BLOCK, 0, st>>>(A);
+    } else {
+        if (!frozen) k_conv_mark<P><<<vg, 256, 0, st>>>(A);
+        if (!frozen) k_conv_close<P><<<vg, 256, 0, st>>>(A);
+        k_conv_gather<P><<<lg, 256, 0, st>>>(A);
+    }
     mark(b, 3);
     HIP_OK(hipGetLastError());
     int rc = 0;
     mark(b, 4);
-    // grid-stride over the static obstacle list (none without walls)
-    int maxo = 0;
-    for (auto *h : b->hs) maxo = std::max(maxo, h->ocount0);
-    if (maxo > 0) k_obstacle_fill<P><<<dim3(std::min(list_blocks(maxN), (maxo + 255) / 256), n), 256, 0, st>>>(A);
-    bool any_bubble = false;
-    for (auto *h : b->hs) any_bubble |= h->bubble != 0;
-    if (any_bubble) {
-        k_bubble_partial<P><<<dim3(VOL_BLOCKS, n), 256, 0, st>>>(A);
-        k_bubble_final<P><<<dim3(1, n), 1024, 0, st>>>(A, VOL_BLOCKS);
-    }
+    if (any_bubble) k_bubble_walls<P><<<dim3(ob + VOL_GRID, n), VOL_NT, 0, st>>>(A, ob);
+    else if (ob > 0 && !walls_with_phi) k_obstacle_fill<P><<<dim3(ob, n), 256, 0, st>>>(A);
     rc = enqueue_geometry<P>(b, A, maxN, 1);
     if (rc) return rc;
     mark(b, 5);
@@ -1952,8 +1963,7 @@ int do_bubble_start(fslbm_lattice *h)
     const Batch<P> A = make_batch<P>(&h->self, maxN, s_, t_);
     const Fields<P> F = make_fields<P>(h);
     k_bubble_arm<<<1, 1, 0, h->stream>>>(F.sc);
-    k_bubble_partial<P><<<dim3(VOL_BLOCKS, 1), 256, 0, h->stream>>>(A);
-    k_bubble_final<P><<<dim3(1, 1), 1024, 0, h->stream>>>(A, VOL_BLOCKS);
+    k_bubble_walls<P><<<dim3(VOL_GRID, 1), VOL_NT, 0, h->stream>>>(A, 0);
     HIP_OK(hipGetLastError());
     return 0;
 }

@@ -78,16 +78,13 @@ __device__ inline int wrap_one(int v, int n) { return v < 0 ? v + n : (v >= n ? 
 // (a new cell from gas is fluid whether it stays in the layer or closes to
 // liquid).
 template <class P>
-__global__ __launch_bounds__(256) void k_conv_mark(const Batch<P> B)
+__device__ inline void conv_mark(const Fields<P> &F, int nc, int wave, int waves)
 {
-    const Fields<P> &F = B.f[blockIdx.y];
-    const int nc = *(volatile const int *)&F.sc->nconv;
-    if (nc == 0) return;
     const uint32_t tag = F.sc->step << 2;
     const uint8_t s8 = uint8_t(tag >> 2);
-    const int lane = threadIdx.x & 63, waves = gridDim.x * 4;
+    const int lane = threadIdx.x & 63;
     const int q = lane < NQ ? lane : 0;  // lanes without a direction read the cell itself
-    for (int c = blockIdx.x * 4 + (threadIdx.x >> 6); c < nc; c += waves) {
+    for (int c = wave; c < nc; c += waves) {
         const int i = F.clist[c];
         const Nbr nb(i, F.nx, F.ny, F.nz);
         const int j = nb.at(dir_x(q), dir_y(q), dir_z(q));
@@ -126,6 +123,13 @@ __global__ __launch_bounds__(256) void k_conv_mark(const Batch<P> B)
             F.near[wrap_one(nb.x + dx, F.nx) + F.nx * (wrap_one(nb.y + dy, F.ny) + F.ny * wrap_one(nb.z + dz, F.nz))] = s8;
         }
     }
+}
+template <class P>
+__global__ __launch_bounds__(256) void k_conv_mark(const Batch<P> B)
+{
+    const Fields<P> &F = B.f[blockIdx.y];
+    const int nc = *(volatile const int *)&F.sc->nconv;
+    if (nc != 0) conv_mark(F, nc, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4);
 }
 
 // Cell type after rules 1-3 (CLOSE_* codes read as interface) from a cell's
@@ -234,13 +238,12 @@ __device__ inline void init_new_cell(const Fields<P> &F, int j, int lane)
 // pass looks two cells out only for a cell without a liquid neighbour after
 // rules 1-3, which is rare. Every old-list cell that leaves the layer is
 // tagged tag | 3, which k_conv_gather tells it by. The new cells' f' (an
-// independent job) rides on the same launch.
+// independent job) rides on the same launch, in its last blocks first, which
+// have no cell of the layer on a small lattice. Block b of nb blocks.
 template <class P>
-__global__ __launch_bounds__(256) void k_conv_close(const Batch<P> B)
+__device__ inline void conv_close(const Fields<P> &F, int b, int nb)
 {
-    const Fields<P> &F = B.f[blockIdx.y];
-    if (F.sc->nconv == 0) return;
-    if (blockIdx.x == 0 && threadIdx.x == 0) {  // counters of the list rebuild in k_conv_gather
+    if (b == 0 && threadIdx.x == 0) {  // counters of the list rebuild in k_conv_gather
         F.sc->nkeep = 0;
         F.sc->done = 0;
         F.sc->bbox[0] = F.nx; F.sc->bbox[1] = F.ny; F.sc->bbox[2] = F.nz;
@@ -248,12 +251,12 @@ __global__ __launch_bounds__(256) void k_conv_close(const Batch<P> B)
     }
     const uint32_t tag = F.sc->step << 2;
     const uint8_t s8 = uint8_t(tag >> 2);
-    const int n = list_count(F.sc), nn = F.sc->nnew;
+    const int n = list_count(F.sc), nn = *(volatile const int *)&F.sc->nnew, nt = blockDim.x;
     const int32_t *list = interface_list(F);
-    for (int m = blockIdx.x * 8 + (int)(threadIdx.x >> 5); m < nn; m += gridDim.x * 8)
+    for (int m = (nb - 1 - b) * (nt >> 5) + (int)(threadIdx.x >> 5); m < nn; m += nb * (nt >> 5))
         init_new_cell(F, F.newlist[m], threadIdx.x & 31);
     const int lane = threadIdx.x & 63;
-    for (int k0 = blockIdx.x * 256; k0 < n + nn; k0 += gridDim.x * 256) {
+    for (int k0 = b * nt; k0 < n + nn; k0 += nb * nt) {
         const int k = k0 + (int)threadIdx.x;
         const int i = k < n + nn ? layer_cell(F, list, k, n) : 0;
         const bool on = k < n + nn && F.near[i] == s8;
@@ -294,6 +297,12 @@ __global__ __launch_bounds__(256) void k_conv_close(const Batch<P> B)
         F.conv[i] = gas ? CV_CLOSE_GAS : CV_CLOSE_LIQ;
         if (k < n) F.mark[i] = tag | 3u;
     }
+}
+template <class P>
+__global__ __launch_bounds__(256) void k_conv_close(const Batch<P> B)
+{
+    const Fields<P> &F = B.f[blockIdx.y];
+    if (F.sc->nconv != 0) conv_close(F, blockIdx.x, gridDim.x);
 }
 
 // Rule 5 for a cell w that leaves the layer: its excess, and the number of
@@ -374,9 +383,10 @@ __device__ inline int block_exclusive_scan(int v, int *lds_wave, int &total)
 }
 
 // Block-wide min / max of a box contribution; thread 0 issues the atomics.
+template <int NT>
 __device__ inline void block_box_update(int (&lo)[3], int (&hi)[3], int *box)
 {
-    __shared__ int red[6][4];
+    __shared__ int red[6][NT / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
 #pragma unroll
     for (int d = 32; d > 0; d >>= 1)
@@ -392,7 +402,7 @@ __device__ inline void block_box_update(int (&lo)[3], int (&hi)[3], int *box)
         }
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 4; ++w)
+        for (int w = 1; w < NT / 64; ++w)
             for (int c = 0; c < 3; ++c) {
                 red[c][0] = min(red[c][0], red[c][w]);
                 red[3 + c][0] = max(red[3 + c][0], red[3 + c][w]);
@@ -422,17 +432,15 @@ __device__ inline void box_add(const Fields<P> &F, int i, int (&lo)[3], int (&hi
 // current. The order of the list does not enter any result (every per-cell
 // computation is independent). Also sets phi = m / rho of every interface
 // cell for the new time level, so it runs in every step; without conversions
-// that is all it does.
-template <class P>
-__global__ __launch_bounds__(256) void k_conv_gather(const Batch<P> B)
+// that is all it does. Block b of nb blocks of NT threads.
+template <class P, int NT>
+__device__ inline void conv_gather(const Fields<P> &F, bool frozen, int b, int nb)
 {
-    const Fields<P> &F = B.f[blockIdx.y];
     using R = typename P::R;
     const int n = list_count(F.sc);
     const int32_t *list = interface_list(F);
     if (F.sc->nconv == 0) {
-        const bool frozen = B.p[blockIdx.y].frozen != 0;
-        for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
+        for (int k = b * NT + threadIdx.x; k < n; k += nb * NT) {
             const int i = list[k];
             const R ph = F.m[i] / F.rho[i];
             F.phi[i] = ph;
@@ -447,14 +455,14 @@ __global__ __launch_bounds__(256) void k_conv_gather(const Batch<P> B)
         }
         return;
     }
-    __shared__ int lw[4];
+    __shared__ int lw[NT / 64];
     __shared__ int base_s;
     const uint32_t tag = F.sc->step << 2;
     const uint8_t s8 = uint8_t(tag >> 2);
-    const int nl = n + F.sc->nnew;
+    const int nl = n + *(volatile const int *)&F.sc->nnew;
     int32_t *out = F.sc->lsel ? F.ilist : F.ilist_tmp;
     int lo[3] = {1 << 30, 1 << 30, 1 << 30}, hi[3] = {-1, -1, -1};
-    for (int k0 = blockIdx.x * 256; k0 < nl; k0 += gridDim.x * 256) {
+    for (int k0 = b * NT; k0 < nl; k0 += nb * NT) {
         const int k = k0 + (int)threadIdx.x;
         bool keep = false;
         int i = 0;
@@ -484,14 +492,50 @@ __global__ __launch_bounds__(256) void k_conv_gather(const Batch<P> B)
             box_add(F, i, lo, hi);
         }
     }
-    block_box_update(lo, hi, F.sc->bbox);
+    block_box_update<NT>(lo, hi, F.sc->bbox);
+    // no fence (it would write the whole L2 back): the last block reads
+    // nothing of the others but nkeep, whose additions have returned before
+    // their blocks count themselves here
     if (threadIdx.x == 0) {
-        __threadfence();
-        if (atomicAdd(&F.sc->done, 1) == (int)gridDim.x - 1) {
+        if (atomicAdd(&F.sc->done, 1) == nb - 1) {
             F.sc->icount = atomicAdd(&F.sc->nkeep, 0);
             F.sc->lsel ^= 1;
         }
     }
+}
+template <class P>
+__global__ __launch_bounds__(256) void k_conv_gather(const Batch<P> B)
+{
+    conv_gather<P, 256>(B.f[blockIdx.y], B.p[blockIdx.y].frozen != 0, blockIdx.x, gridDim.x);
+}
+
+// The whole chain of a small layer in one block per lattice: the phases of
+// the three launches above with barriers between them. A step without
+// conversions is then one launch instead of three (each costs about 3 us on
+// the device whatever it does). The fence drops what the CU's cache
+// holds of the words that the phase before changed by atomics. The host
+// takes it for lattices of at most CONV_BLOCK_CELLS interface cells (one
+// thread each): there a few converting cells fit the block's 16 wavefronts.
+// Per pass, FP64: droplet 24^3 (5 steps) 204 -> 180 us; 48^3 bubble between
+// walls (20 steps, with the launch that the walls share with the volume sum)
+// 1157 -> 925 us.
+constexpr int CONV_BLOCK = 1024;
+constexpr int CONV_BLOCK_CELLS = 1024;
+
+template <class P>
+__global__ __launch_bounds__(CONV_BLOCK) void k_conv_block(const Batch<P> B)
+{
+    const Fields<P> &F = B.f[blockIdx.y];
+    const int nc = *(volatile const int *)&F.sc->nconv;
+    if (nc != 0) {
+        conv_mark(F, nc, threadIdx.x >> 6, CONV_BLOCK / 64);
+        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        conv_close(F, 0, 1);
+        __syncthreads();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    }
+    conv_gather<P, CONV_BLOCK>(F, B.p[blockIdx.y].frozen != 0, 0, 1);
 }
 
 // The current list back into ilist (state copies hold that buffer alone):
@@ -668,34 +712,55 @@ __global__ __launch_bounds__(256) void k_mark_wall_cells(const uint8_t *flags, u
 // neighbours with aperture |nw.c^_q| > sqrt(2)/2 (strict; the 45-degree
 // links are excluded), nw the normalised sum of the directions from x_o to
 // its non-obstacle neighbours.
-template <class P>
-__global__ __launch_bounds__(256) void k_obstacle_fill(const Batch<P> B)
+// The 18 types of a cell come in together, then the 18 fill levels of a cell
+// with a fluid neighbour (away from the liquid most have none). FROM_M: the
+// interface cells' fill levels are computed from m and rho, with
+// k_conv_gather's division, so that the fill does not wait for that kernel;
+// only for steps in which no cell converts. Thread t of nt.
+template <class P, bool FROM_M>
+__device__ inline void obstacle_fill(const Fields<P> &F, int t, int nt)
 {
-    const Fields<P> &F = B.f[blockIdx.y];
     using R = typename P::R;
     const int n = F.sc->ocount;
     const double alpha = 0.70710678118654752440 + 1e-12;
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
+    for (int k = t; k < n; k += nt) {
         const int i = F.olist[k];
         const Nbr nb(i, F.nx, F.ny, F.nz);
-        int sx = 0, sy = 0, sz = 0;
+        uint8_t fl[NQ];
 #pragma unroll
-        for (int q = 1; q < NQ; ++q)
-            if (!(F.flags[nb.at(dir_x(q), dir_y(q), dir_z(q))] & FL_OBST)) {
+        for (int q = 1; q < NQ; ++q) fl[q] = F.flags[nb.at(dir_x(q), dir_y(q), dir_z(q))];
+        int sx = 0, sy = 0, sz = 0;
+        bool fluid = false;
+#pragma unroll
+        for (int q = 1; q < NQ; ++q) {
+            fluid |= (fl[q] & FL_FLUID) != 0;
+            if (!(fl[q] & FL_OBST)) {
                 sx += dir_x(q); sy += dir_y(q); sz += dir_z(q);
             }
-        const double len = sqrt(double(sx * sx + sy * sy + sz * sz));
+        }
         double num = 0, den = 0;
-        if (len > 0) {
-            const double wx = sx / len, wy = sy / len, wz = sz / len;
+        if (fluid && (sx | sy | sz) != 0) {
+            R ph[NQ], m[NQ], rho[NQ];
 #pragma unroll
             for (int q = 1; q < NQ; ++q) {
                 const int j = nb.at(dir_x(q), dir_y(q), dir_z(q));
-                if (!(F.flags[j] & FL_FLUID)) continue;
+                ph[q] = F.phi[j];
+                if constexpr (FROM_M) {
+                    m[q] = F.m[j];
+                    rho[q] = F.rho[j];
+                }
+            }
+            const double len = sqrt(double(sx * sx + sy * sy + sz * sz));
+            const double wx = sx / len, wy = sy / len, wz = sz / len;
+#pragma unroll
+            for (int q = 1; q < NQ; ++q) {
+                if (!(fl[q] & FL_FLUID)) continue;
                 const double cl = sqrt(double(dir_len2(q)));
                 const double w = fabs((wx * dir_x(q) + wy * dir_y(q) + wz * dir_z(q)) / cl);
                 if (w > alpha) {
-                    num += w * double(F.phi[j]);
+                    if constexpr (FROM_M)
+                        if (fl[q] & FL_IF) ph[q] = m[q] / rho[q];
+                    num += w * double(ph[q]);
                     den += w;
                 }
             }
@@ -704,29 +769,58 @@ __global__ __launch_bounds__(256) void k_obstacle_fill(const Batch<P> B)
         if (F.snap) F.snap[(size_t)SNAP * F.sc->icount + k] = R(den > 0 ? num / den : 0.0);
     }
 }
+template <class P>
+__global__ __launch_bounds__(256) void k_obstacle_fill(const Batch<P> B)
+{
+    obstacle_fill<P, false>(B.f[blockIdx.y], blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
+}
+
+// phi = m / rho (blocks before ng) and the obstacle fill (the others) of a
+// step with frozen cell types in one launch: 5.0 us on the 128^3 sessile drop,
+// 4.7 + 5.3 in two (window and gradients of 40 steps 6030 -> 5750 us).
+template <class P>
+__global__ __launch_bounds__(256) void k_gather_walls(const Batch<P> B, int ng)
+{
+    const int b = blockIdx.x;
+    if (b < ng) conv_gather<P, 256>(B.f[blockIdx.y], true, b, ng);
+    else obstacle_fill<P, true>(B.f[blockIdx.y], (b - ng) * 256 + threadIdx.x, ((int)gridDim.x - ng) * 256);
+}
 
 // ------------------------------------------------ bubble model (Sec. III.A.1)
 // The whole gas of a lattice is one bubble with isothermal pressure,
 // p_g(t) V(t) = p_g(0) V(0), so rho_gas(t) = rho_gas V0 / V(t) with the gas
 // volume V = (non-obstacle cells) - (liquid cells + sum of phi over
 // interface cells). The liquid volume is summed over the fluid box in a
-// fixed partition (VOL_BLOCKS blocks, fixed order within each), after the
+// fixed partition (VOL_CHUNKS chunks, fixed order within each), after the
 // step's conversions.
-constexpr int VOL_BLOCKS = 1024;
+// Four chunks to a block, and the block that finishes last adds the chunk
+// sums and sets rho_gas(t): no launch of its own. The obstacle fill (blocks
+// before `nw`) reads other cells than it writes and none of the sum's, so the
+// two share a launch. Per launch 10.8 us on the 96^3 bubble between walls
+// (FP64), where fill, chunk sums and final sum took 4.9 + 5.7 + 4.1 in three.
+constexpr int VOL_CHUNKS = 1024;
+constexpr int VOL_NT = 1024;                       // threads per block, 256 to a chunk
+constexpr int VOL_GRID = VOL_CHUNKS / (VOL_NT / 256);
 
 template <class P>
-__global__ __launch_bounds__(256) void k_bubble_partial(const Batch<P> B)
+__global__ __launch_bounds__(VOL_NT) void k_bubble_walls(const Batch<P> B, int nw)
 {
+    const Fields<P> &F = B.f[blockIdx.y];
+    if ((int)blockIdx.x < nw) {  // 256 cells to a block: the loads of a wavefront per SIMD
+        if (threadIdx.x < 256) obstacle_fill<P, false>(F, blockIdx.x * 256 + threadIdx.x, nw * 256);
+        return;
+    }
     const Params &prm = B.p[blockIdx.y];
     if (!prm.bubble) return;
-    const Fields<P> &F = B.f[blockIdx.y];
-    __shared__ double s[256];
+    __shared__ double s[VOL_NT];
+    __shared__ int last;
+    const int t = threadIdx.x & 255, c = ((int)blockIdx.x - nw) * (VOL_NT / 256) + (int)(threadIdx.x >> 8);
     const CellRange box = CellRange::from(F.sc->fbox);
     const int n = box.size();
-    const int chunk = (n + gridDim.x - 1) / gridDim.x;
-    const int b0 = min(n, (int)blockIdx.x * chunk), b1 = min(n, b0 + chunk);
+    const int chunk = (n + VOL_CHUNKS - 1) / VOL_CHUNKS;
+    const int b0 = min(n, c * chunk), b1 = min(n, b0 + chunk);
     double acc = 0.0;
-    for (int k = b0 + threadIdx.x; k < b1; k += 256) {
+    for (int k = b0 + t; k < b1; k += 256) {
         const int i = box.cell(k, F.nx, F.ny);
         const uint8_t fl = F.flags[i];
         if (fl & FL_LIQ) acc += 1.0;
@@ -735,22 +829,24 @@ __global__ __launch_bounds__(256) void k_bubble_partial(const Batch<P> B)
     s[threadIdx.x] = acc;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
-        if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
+        if (t < w) s[threadIdx.x] += s[threadIdx.x + w];
         __syncthreads();
     }
-    if (threadIdx.x == 0) F.part[blockIdx.x] = s[0];
-}
-
-template <class P>
-__global__ __launch_bounds__(1024) void k_bubble_final(const Batch<P> B, int nblocks)
-{
-    const Params &prm = B.p[blockIdx.y];
-    if (!prm.bubble) return;
-    const Fields<P> &F = B.f[blockIdx.y];
-    __shared__ double s[1024];
-    s[threadIdx.x] = (int)threadIdx.x < nblocks ? F.part[threadIdx.x] : 0.0;
+    // the chunk sums go by atomic exchanges, which have taken effect for the
+    // whole device when they return: no fence, which would write the L2 back
+    // in each of the 256 blocks (12 us)
+    auto *part = reinterpret_cast<unsigned long long *>(F.part);
+    if (t == 0) {
+        const unsigned long long was = atomicExch(&part[c], (unsigned long long)__double_as_longlong(s[threadIdx.x]));
+        asm volatile("" ::"v"(was));  // waits for the return
+    }
     __syncthreads();
-    for (int w = 512; w > 0; w >>= 1) {
+    if (threadIdx.x == 0) last = atomicInc(&F.sc->vdone, unsigned(VOL_GRID - 1)) == unsigned(VOL_GRID - 1);
+    __syncthreads();
+    if (!last) return;
+    s[threadIdx.x] = __longlong_as_double((long long)atomicOr(&part[threadIdx.x], 0ull));
+    __syncthreads();
+    for (int w = VOL_NT / 2; w > 0; w >>= 1) {
         if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
         __syncthreads();
     }

@@ -260,6 +260,7 @@ struct DevScalars {
     // not part of a saved state (a saved list is always in ilist)
     int lsel;           // 1: the interface list is in ilist_tmp, 0: in ilist
     int done;           // blocks of k_conv_gather that have finished
+    unsigned vdone;     // blocks of the volume sum that have finished (0 between launches)
 };
 
 // A box of cells [x0, x0+ex) x [y0, y0+ey) x [z0, z0+ez) enumerated with x
