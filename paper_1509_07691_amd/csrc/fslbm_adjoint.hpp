@@ -143,10 +143,15 @@ __device__ inline double reflected_phib(const Fields<P> &F, const Adj &A, int k,
     if (!(F.flags[i] & FL_NEAR_OBST)) return 0.0;
     const Nbr ni(i, F.nx, F.ny, F.nz);
     const double *c = A.refl + (size_t)(NQ - 1) * k;
-    double acc = 0.0;
+    double w[NQ], pb[NQ], acc = 0.0;  // all loaded first: one wait
+#pragma unroll
+    for (int q = 1; q < NQ; ++q) {
+        w[q] = c[q - 1];
+        pb[q] = A.phib[ni.at(dir_x(q), dir_y(q), dir_z(q))];
+    }
 #pragma unroll
     for (int q = 1; q < NQ; ++q)
-        if (c[q - 1] != 0.0) acc += A.phib[ni.at(dir_x(q), dir_y(q), dir_z(q))] * c[q - 1];
+        if (w[q] != 0.0) acc += pb[q] * w[q];
     return acc;
 }
 
@@ -173,15 +178,19 @@ __global__ __launch_bounds__(256) void k_adj_prepass(Fields<P> F, Adj A, const t
 {
     const int n = F.sc->icount, no = F.sc->ocount;
     const size_t N = F.N;
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < n + no; k += gridDim.x * 256) {
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n + no; k += gridDim.x * blockDim.x) {
         if (k < n) {
+            // every load before the first store: they travel together
             const int i = interface_list(F)[k];
             const double m = double(snap_next[(size_t)SNAP * k]), r = double(snap_next[(size_t)SNAP * k + 1]);
+            typename P::R s[SNAP];
+#pragma unroll
+            for (int e = 0; e < SNAP; ++e) s[e] = snap_cur[(size_t)SNAP * k + e];
+            const double mb = A.mbar[i];
             const double pb = A.phib[i] + reflected_phib(F, A, k, i);
-            A.mbar[i] += pb / r;
+            A.mbar[i] = mb + pb / r;
             A.rhob[i] = -pb * m / (r * r);
             A.phib[i] = 0.0;
-            const typename P::R *s = snap_cur + (size_t)SNAP * k;
             F.m[i] = s[0]; F.rho[i] = s[1]; F.phi[i] = s[2]; F.K[i] = s[3];
             F.nrm[i] = s[4]; F.nrm[N + i] = s[5]; F.nrm[2 * N + i] = s[6]; F.plic[i] = s[7];
         } else {
@@ -473,7 +482,7 @@ template <class P>
 __global__ __launch_bounds__(256) void k_adj_fd_mol(const Fields<P> F, const Adj A)
 {
     const GrownBox box(F, FD_GROW);
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < box.r.size(); k += gridDim.x * 256) {
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < box.r.size(); k += gridDim.x * blockDim.x) {
         const Nbr nb = box.at(k);
         const int i = nb.at(0, 0, 0);
         double s = 0.0;
@@ -565,7 +574,7 @@ __global__ __launch_bounds__(256) void k_adj_fd_nbar(const Fields<P> F, const Ad
     const size_t N = F.N;
     const bool walls = F.sc->ocount > 0;
     const GrownBox box(F, FD_GROW);
-    for (int c = blockIdx.x * 256 + threadIdx.x; c < box.r.size(); c += gridDim.x * 256) {
+    for (int c = blockIdx.x * blockDim.x + threadIdx.x; c < box.r.size(); c += gridDim.x * blockDim.x) {
         const Nbr nb = box.at(c);
         const int i = nb.at(0, 0, 0);
         const uint8_t fl = F.flags[i];
@@ -639,7 +648,7 @@ template <class P>
 __global__ __launch_bounds__(256) void k_adj_fd_msb(const Fields<P> F, const Adj A)
 {
     const GrownBox box(F, FD_GROW);
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < box.r.size(); k += gridDim.x * 256) {
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < box.r.size(); k += gridDim.x * blockDim.x) {
         const Nbr nb = box.at(k);
         const int i = nb.at(0, 0, 0);
         A.msb[i] = py_div_t(A.gb, F.N, nb);
@@ -652,7 +661,7 @@ template <class P>
 __global__ __launch_bounds__(256) void k_adj_fd_phib(const Fields<P> F, const Adj A)
 {
     const GrownBox box(F, FD_GROW);
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < box.r.size(); k += gridDim.x * 256) {
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < box.r.size(); k += gridDim.x * blockDim.x) {
         const Nbr nb = box.at(k);
         const int i = nb.at(0, 0, 0);
         const uint8_t fl = F.flags[i];
@@ -1330,21 +1339,45 @@ __global__ __launch_bounds__(256) void k_adj_lsqr_plic(const Fields<P> F, const 
         const int j = interface_list(F)[k];
         const Nbr nb(j, F.nx, F.ny, F.nz);
         double nbar[3] = {0, 0, 0}, abar = 0, g[3] = {0, 0, 0};
-        for (int s = lane; s < 27; s += ADJ_LANES) {
+        // the loads of both rounds and of lane 0's later chain first, then
+        // the partials that they point at
+        constexpr int RO = (27 + ADJ_LANES - 1) / ADJ_LANES;
+        bool on[RO];
+        size_t at[RO];
+        double ph[RO];
+#pragma unroll
+        for (int u = 0; u < RO; ++u) {
+            const int s = lane + u * ADJ_LANES < 27 ? lane + u * ADJ_LANES : 13;
             const int a = s % 3 - 1, b = (s / 3) % 3 - 1, c = s / 9 - 1;
             const int i = nb.at(-a, -b, -c);  // j = i + (a, b, c)
-            if (F.flags[i] & FL_IF) {
-                const double *cs = A.contrib + (size_t)CONTRIB * A.pos[i] + 4 * s;
+            on[u] = lane + u * ADJ_LANES < 27 && (F.flags[i] & FL_IF);
+            at[u] = (size_t)CONTRIB * A.pos[i] + 4 * s;
+            ph[u] = double(F.phi[nb.at(a, b, c)]);
+        }
+        double nj[3] = {0, 0, 0}, dphi = 0, dn[3] = {0, 0, 0};
+        if (lane == 0) {
+            dphi = A.ms[j];
+            for (int d = 0; d < 3; ++d) {
+                nj[d] = double(F.nrm[d * N + j]);
+                dn[d] = A.gb[d * N + j];  // plic_derivs_blocks
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < RO; ++u) {
+            const int s = lane + u * ADJ_LANES;
+            if (s >= 27) continue;
+            const int a = s % 3 - 1, b = (s / 3) % 3 - 1, c = s / 9 - 1;
+            if (on[u]) {
+                const double *cs = A.contrib + at[u];
                 nbar[0] += cs[0];
                 nbar[1] += cs[1];
                 nbar[2] += cs[2];
                 abar += cs[3];
             }
             // PY weights: central difference along one axis, (1, 2, 1) across
-            const double ph = double(F.phi[nb.at(a, b, c)]);
-            g[0] += a * pyw(b) * pyw(c) * ph;
-            g[1] += b * pyw(a) * pyw(c) * ph;
-            g[2] += c * pyw(a) * pyw(b) * ph;
+            g[0] += a * pyw(b) * pyw(c) * ph[u];
+            g[1] += b * pyw(a) * pyw(c) * ph[u];
+            g[2] += c * pyw(a) * pyw(b) * ph[u];
         }
         for (int d = 0; d < 3; ++d) {
             nbar[d] = group_sum<ADJ_LANES>(nbar[d]);
@@ -1352,10 +1385,8 @@ __global__ __launch_bounds__(256) void k_adj_lsqr_plic(const Fields<P> F, const 
         }
         abar = group_sum<ADJ_LANES>(abar);
         if (lane != 0) continue;
-        const double nj[3] = {double(F.nrm[j]), double(F.nrm[N + j]), double(F.nrm[2 * N + j])};
         double o[3] = {0, 0, 0};
         if (nj[0] != 0.0 || nj[1] != 0.0 || nj[2] != 0.0) {
-            const double dphi = A.ms[j], dn[3] = {A.gb[j], A.gb[N + j], A.gb[2 * N + j]};  // plic_derivs_blocks
             A.phib[j] += abar * dphi;
             for (int d = 0; d < 3; ++d) nbar[d] += abar * dn[d];
             const double len = sqrt(g[0] * g[0] + g[1] * g[1] + g[2] * g[2]);
@@ -1379,7 +1410,7 @@ __global__ __launch_bounds__(256) void k_adj_lsqr_phib(const Fields<P> F, const 
     const int n = F.sc->icount, no = F.sc->ocount;
     const GrownBox box(F, 2);  // gb is not zero at interface cells only
     auto off = [](int v, int o, int n) { return v < o ? v - o + n : v - o; };
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < n + no; k += gridDim.x * 256) {
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n + no; k += gridDim.x * blockDim.x) {
         const int i = k < n ? interface_list(F)[k] : F.olist[k - n];
         const Nbr nb(i, F.nx, F.ny, F.nz);
         if (off(nb.x, box.r.x0, F.nx) >= box.r.ex || off(nb.y, box.r.y0, F.ny) >= box.r.ey ||

@@ -298,9 +298,10 @@ inline int cell_blocks(int N) { return (N + 255) / 256; }
 inline int list_blocks(int N) { return std::min(LIST_GRID, std::max(1, (N + 255) / 256)); }
 inline int cmp_blocks(int N) { return std::min(CMP_GRID, (N + CMP_CELLS - 1) / CMP_CELLS); }
 constexpr int GEOM_GRID = 1024;  // blocks per lattice of the tiled geometry kernels
-// least blocks of the two kernels that spread converting cells over
-// wavefronts (4 and 8 cells per block): a step converts up to a few hundred
-// cells of a small lattice too
+// blocks, beside those of the list, of the two kernels that spread converting
+// cells over wavefronts (4 and 8 cells per block): a step converts up to a few
+// hundred cells of a small lattice too, and new cells go to blocks without
+// cells of the layer
 constexpr int CONV_GRID = 64;
 constexpr int SC_LIST_GRID = 1024;  // blocks per lattice of the interface / wall-list stream-collide
 
@@ -925,12 +926,13 @@ inline hipStream_t bstream(const fslbm_batch *b) { return b->hs[0]->stream; }
 
 // Grid of the interface-list kernels of a batch: about one thread per
 // interface cell at creation (the loops are grid-stride, so later growth is
-// still covered), at least 8 and at most 512 blocks per lattice.
-inline int batch_list_blocks(const fslbm_batch *b, int cells_per_block)
+// still covered), at least 8 and at most 512 blocks of 256 threads (their
+// like in blocks of nt) per lattice.
+inline int batch_list_blocks(const fslbm_batch *b, int cells_per_block, int nt = 256)
 {
     int m = 0;
     for (auto *h : b->hs) m = std::max(m, h->icount0);
-    return std::min(512, std::max(8, (m + cells_per_block - 1) / cells_per_block));
+    return std::min(512 * 256 / nt, std::max(8 * 256 / nt, (m + cells_per_block - 1) / cells_per_block));
 }
 
 template <class P>
@@ -964,7 +966,7 @@ int enqueue_geometry(const fslbm_batch *b, const Batch<P> &A, int maxN, int eos 
         any_tr |= h->curv == FSLBM_CURV_TR;
     }
     const bool any_plic = any_lsqr || any_tr;
-    const dim3 cg4(batch_list_blocks(b, 64), n), cgt(batch_list_blocks(b, 256 / TR_LANES), n);
+    const dim3 cg4(batch_list_blocks(b, LIST_NT / 4, LIST_NT), n), cgt(batch_list_blocks(b, 256 / TR_LANES), n);
     // FD contact normals exist only next to walls
     if (any_fd_wall) {
         k_fd_contact_normals<P><<<dim3(list_blocks(maxN), n), 256, 0, st>>>(A, eos);
@@ -973,9 +975,9 @@ int enqueue_geometry(const fslbm_batch *b, const Batch<P> &A, int maxN, int eos 
     if (any_fd && any_plic) k_geometry_mixed<P><<<tg, 256, 0, st>>>(A, eos);
     else if (any_fd && fd_cells <= FD_FEW_CELLS) k_geometry_fd<P, 512><<<tg, 512, 0, st>>>(A, eos);
     else if (any_fd) k_geometry_fd<P, 256><<<tg, 256, 0, st>>>(A, eos);
-    else k_normals_plic<P><<<dim3(batch_list_blocks(b, 256), n), 256, 0, st>>>(A, eos);
-    if (any_lsqr && stored) k_curv_lsqr4<P, true><<<cg4, 256, 0, st>>>(A);
-    else if (any_lsqr) k_curv_lsqr4<P, false><<<cg4, 256, 0, st>>>(A);
+    else k_normals_plic<P><<<dim3(batch_list_blocks(b, LIST_NT, LIST_NT), n), LIST_NT, 0, st>>>(A, eos);
+    if (any_lsqr && stored) k_curv_lsqr4<P, true><<<cg4, LIST_NT, 0, st>>>(A);
+    else if (any_lsqr) k_curv_lsqr4<P, false><<<cg4, LIST_NT, 0, st>>>(A);
     if (any_tr) k_curv_tr<P><<<cgt, 256, 0, st>>>(A);
     HIP_OK(hipGetLastError());
     return 0;
@@ -1035,7 +1037,7 @@ int enqueue_step_kernels(fslbm_batch *b, const void *fsrc = nullptr, void *fdst 
     int boxb = 1;
     for (auto *h : b->hs) boxb = std::max(boxb, h->box_blocks);
     const dim3 cg(boxb, n), sg(std::min(SC_LIST_GRID, cell_blocks(maxN)), n),
-        lg(batch_list_blocks(b, 256), n), vg(std::max(CONV_GRID, batch_list_blocks(b, 256)), n);
+        lg(batch_list_blocks(b, 256), n), vg(CONV_GRID + batch_list_blocks(b, 256), n);
     mark(b, 0);
     b->split_last = split_now<P>(b) ? 1 : 0;
     if (b->split_last) {
@@ -1064,9 +1066,10 @@ int enqueue_step_kernels(fslbm_batch *b, const void *fsrc = nullptr, void *fdst 
         any_bubble |= h->bubble != 0;
     }
     const int ob = maxo > 0 ? std::min(list_blocks(maxN), (maxo + 255) / 256) : 0;
-    const bool walls_with_phi = frozen && ob > 0 && !any_bubble;
-    if (walls_with_phi) {
-        k_gather_walls<P><<<dim3(lg.x + ob, n), 256, 0, st>>>(A, (int)lg.x);
+    const bool frozen_walls = frozen && !any_bubble;
+    if (frozen_walls) {
+        const int ng = batch_list_blocks(b, LIST_NT, LIST_NT);
+        k_gather_walls<P><<<dim3(ng + ob * (256 / LIST_NT), n), LIST_NT, 0, st>>>(A, ng);
     } else if (!frozen && maxi <= CONV_BLOCK_CELLS) {
         k_conv_block<P><<<dim3(1, n), CONV_BLOCK, 0, st>>>(A);
     } else {
@@ -1079,7 +1082,7 @@ int enqueue_step_kernels(fslbm_batch *b, const void *fsrc = nullptr, void *fdst 
     int rc = 0;
     mark(b, 4);
     if (any_bubble) k_bubble_walls<P><<<dim3(ob + VOL_GRID, n), VOL_NT, 0, st>>>(A, ob);
-    else if (ob > 0 && !walls_with_phi) k_obstacle_fill<P><<<dim3(ob, n), 256, 0, st>>>(A);
+    else if (ob > 0 && !frozen_walls) k_obstacle_fill<P><<<dim3(ob * (256 / LIST_NT), n), LIST_NT, 0, st>>>(A);
     rc = enqueue_geometry<P>(b, A, maxN, 1);
     if (rc) return rc;
     mark(b, 5);
@@ -1724,16 +1727,16 @@ int enqueue_geometry_adjoint(fslbm_lattice *h, const Fields<P> &F, const Adj &A,
     const int N = h->N;
     const int cg = std::min(4096, cell_blocks(N)), lg = list_blocks(N);
     if (h->curv == FSLBM_CURV_FD) {
-        k_adj_fd_mol<P><<<cg, 256, 0, st>>>(F, A);
-        k_adj_fd_nbar<P><<<cg, 256, 0, st>>>(F, A, prm);
-        k_adj_fd_msb<P><<<cg, 256, 0, st>>>(F, A);
-        k_adj_fd_phib<P><<<cg, 256, 0, st>>>(F, A);
+        k_adj_fd_mol<P><<<cg * (256 / LIST_NT), LIST_NT, 0, st>>>(F, A);
+        k_adj_fd_nbar<P><<<cg * (256 / LIST_NT), LIST_NT, 0, st>>>(F, A, prm);
+        k_adj_fd_msb<P><<<cg * (256 / LIST_NT), LIST_NT, 0, st>>>(F, A);
+        k_adj_fd_phib<P><<<cg * (256 / LIST_NT), LIST_NT, 0, st>>>(F, A);
     } else {
         const int cpb = 256 / ADJ_LANES;  // interface cells per block
         const int l8 = std::min(2048, std::max(1, (h->adj.icount + cpb - 1) / cpb));
         k_adj_lsqr_cell<P><<<l8 + lg, 256, 0, st>>>(F, A, prm, l8);
         k_adj_lsqr_plic<P><<<l8, 256, 0, st>>>(F, A);
-        k_adj_lsqr_phib<P><<<lg, 256, 0, st>>>(F, A);
+        k_adj_lsqr_phib<P><<<lg * (256 / LIST_NT), LIST_NT, 0, st>>>(F, A);
     }
     HIP_OK(hipGetLastError());
     return 0;
@@ -1870,7 +1873,7 @@ int do_adj_backward(fslbm_lattice *h, const double *dphi, int in_dev, double *ds
         for (long long t = t1 - 1; t >= t0 && !rc; --t) {
             const Slot cur = seg_slot(w, s, t), nxt = seg_slot(w, s, t + 1);
             Fields<P> F = make_fields<P>(h);
-            k_adj_prepass<P><<<lg, 256, 0, st>>>(F, A, (const typename P::R *)nxt.snap,
+            k_adj_prepass<P><<<lg * (256 / LIST_NT), LIST_NT, 0, st>>>(F, A, (const typename P::R *)nxt.snap,
                                                  (const typename P::R *)cur.snap);
             F.fsrc = (const typename P::S *)cur.f;
             A = adj_fields(w, h, par);

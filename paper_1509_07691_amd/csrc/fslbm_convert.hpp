@@ -47,7 +47,16 @@
 
 namespace fslbm {
 
-constexpr int LIST_GRID = 256;  // blocks per lattice of the grid-stride list kernels
+constexpr int LIST_GRID = 256;  // blocks per lattice of the grid-stride list kernels (of 256 threads)
+// Threads of a block of the list kernels whose threads work alone (gradients
+// and stencils over list cells: some 50 scattered loads a thread). A list
+// holds tens to a thousand wavefronts: blocks of one wavefront spread them
+// over the CUs, where four to a block share one CU's cache and leave most of
+// the others idle. Per launch, 256 -> 64 threads: reverse pass over phi = m / rho
+// 7.6 -> 5.0 us and transposed gradient 8.9 -> 5.8 (128^3 sessile drop; both
+// with their loads moved ahead), normals 7.1 -> 6.2 there and 9.4 -> 8.3 on
+// the 256 x 256 x 128 drop; the LSQR fit, bound by its FP64 chain, is equal.
+constexpr int LIST_NT = 64;
 
 __device__ inline int list_count(const DevScalars *sc) { return *(volatile const int *)&sc->icount; }
 
@@ -772,18 +781,18 @@ __device__ inline void obstacle_fill(const Fields<P> &F, int t, int nt)
 template <class P>
 __global__ __launch_bounds__(256) void k_obstacle_fill(const Batch<P> B)
 {
-    obstacle_fill<P, false>(B.f[blockIdx.y], blockIdx.x * 256 + threadIdx.x, gridDim.x * 256);
+    obstacle_fill<P, false>(B.f[blockIdx.y], blockIdx.x * blockDim.x + threadIdx.x, gridDim.x * blockDim.x);
 }
 
-// phi = m / rho (blocks before ng) and the obstacle fill (the others) of a
-// step with frozen cell types in one launch: 5.0 us on the 128^3 sessile drop,
-// 4.7 + 5.3 in two (window and gradients of 40 steps 6030 -> 5750 us).
+// phi = m / rho (blocks before ng) and the obstacle fill (the others, none
+// without walls) of a step with frozen cell types in one launch: 5.0 us on
+// the 128^3 sessile drop, 4.7 + 5.3 in two.
 template <class P>
-__global__ __launch_bounds__(256) void k_gather_walls(const Batch<P> B, int ng)
+__global__ __launch_bounds__(LIST_NT) void k_gather_walls(const Batch<P> B, int ng)
 {
     const int b = blockIdx.x;
-    if (b < ng) conv_gather<P, 256>(B.f[blockIdx.y], true, b, ng);
-    else obstacle_fill<P, true>(B.f[blockIdx.y], (b - ng) * 256 + threadIdx.x, ((int)gridDim.x - ng) * 256);
+    if (b < ng) conv_gather<P, LIST_NT>(B.f[blockIdx.y], true, b, ng);
+    else obstacle_fill<P, true>(B.f[blockIdx.y], (b - ng) * LIST_NT + threadIdx.x, ((int)gridDim.x - ng) * LIST_NT);
 }
 
 // ------------------------------------------------ bubble model (Sec. III.A.1)

@@ -953,7 +953,7 @@ __device__ inline void normals_plic_list(const Fields<P> &F, const Params &prm)
     using G = typename P::G;
     const int n = list_count(F.sc);
     const int32_t *list = interface_list(F);
-    for (int k = blockIdx.x * 256 + threadIdx.x; k < n; k += gridDim.x * 256) {
+    for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n; k += gridDim.x * blockDim.x) {
         const int i = list[k];
         const Nbr nb(i, F.nx, F.ny, F.nz);
         const uint8_t fl = F.flags[i];
@@ -1028,7 +1028,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
     const size_t N = F.N;
     const int l = threadIdx.x & 3;
     constexpr int ROWS = 7;
-    for (int k = blockIdx.x * 64 + (threadIdx.x >> 2); k < n; k += gridDim.x * 64) {
+    const int per = blockDim.x >> 2;  // cells per block
+    for (int k = blockIdx.x * per + (threadIdx.x >> 2); k < n; k += gridDim.x * per) {
         const int i = list[k];
         const int yz = i / F.nx, x = i - yz * F.nx, z = yz / F.ny, y = yz - z * F.ny;
         const R c0 = F.nrm[i], c1 = F.nrm[N + i], c2 = F.nrm[2 * N + i], ca = F.plic[i];
