@@ -303,6 +303,12 @@ constexpr int GEOM_GRID = 1024;  // blocks per lattice of the tiled geometry ker
 // hundred cells of a small lattice too, and new cells go to blocks without
 // cells of the layer
 constexpr int CONV_GRID = 64;
+// up to one wavefront of layer cells per CU the first two launches of the
+// chain use blocks of LIST_NT threads (closure on the moving 97 x 61 x 83
+// bubble, 3200 cells: 9.5 us, 12.6 with 256); with more, every CU has work
+// anyway. The gather keeps 256: its blocks count their kept cells and box by
+// atomics (17.5 us there, 19.5 with 64).
+constexpr int CONV_FEW_CELLS = 16384;
 constexpr int SC_LIST_GRID = 1024;  // blocks per lattice of the interface / wall-list stream-collide
 
 // ------------------------------------------------------ init kernels
@@ -1036,8 +1042,7 @@ int enqueue_step_kernels(fslbm_batch *b, const void *fsrc = nullptr, void *fdst 
     // bulk stream-collide: one block per 256 cells of the largest fluid box
     int boxb = 1;
     for (auto *h : b->hs) boxb = std::max(boxb, h->box_blocks);
-    const dim3 cg(boxb, n), sg(std::min(SC_LIST_GRID, cell_blocks(maxN)), n),
-        lg(batch_list_blocks(b, 256), n), vg(CONV_GRID + batch_list_blocks(b, 256), n);
+    const dim3 cg(boxb, n), sg(std::min(SC_LIST_GRID, cell_blocks(maxN)), n);
     mark(b, 0);
     b->split_last = split_now<P>(b) ? 1 : 0;
     if (b->split_last) {
@@ -1059,10 +1064,12 @@ int enqueue_step_kernels(fslbm_batch *b, const void *fsrc = nullptr, void *fdst 
     // without walls); it shares a launch with phi = m / rho in a frozen step,
     // else with the bubble's volume sum where there is one
     int maxo = 0, maxi = 0;
+    long long layer = 0;  // interface cells (at creation) of the batch
     bool any_bubble = false;
     for (auto *h : b->hs) {
         maxo = std::max(maxo, h->ocount0);
         maxi = std::max(maxi, h->icount0);
+        layer += h->icount0;
         any_bubble |= h->bubble != 0;
     }
     const int ob = maxo > 0 ? std::min(list_blocks(maxN), (maxo + 255) / 256) : 0;
@@ -1073,8 +1080,10 @@ int enqueue_step_kernels(fslbm_batch *b, const void *fsrc = nullptr, void *fdst 
     } else if (!frozen && maxi <= CONV_BLOCK_CELLS) {
         k_conv_block<P><<<dim3(1, n), CONV_BLOCK, 0, st>>>(A);
     } else {
-        if (!frozen) k_conv_mark<P><<<vg, 256, 0, st>>>(A);
-        if (!frozen) k_conv_close<P><<<vg, 256, 0, st>>>(A);
+        const int nt = layer <= CONV_FEW_CELLS ? LIST_NT : 256;
+        const dim3 vg((CONV_GRID + batch_list_blocks(b, 256)) * (256 / nt), n), lg(batch_list_blocks(b, 256), n);
+        if (!frozen) k_conv_mark<P><<<vg, nt, 0, st>>>(A);
+        if (!frozen) k_conv_close<P><<<vg, nt, 0, st>>>(A);
         k_conv_gather<P><<<lg, 256, 0, st>>>(A);
     }
     mark(b, 3);

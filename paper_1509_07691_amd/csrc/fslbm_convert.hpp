@@ -34,8 +34,8 @@
 // neighbour), and a cell's neighbour types are loaded together rather than
 // one after the other. Each output value has one writer, or several writers
 // storing the identical value. New cells are tagged in `mark` with the step
-// number, so no clearing pass is needed. Measured per step, FP32: 41 us
-// (7 + 15 + 19) on a bubble carried through 97 x 61 x 83 at u = 0.05, 22 us
+// number, so no clearing pass is needed. Measured per step, FP32: 34 us
+// (7 + 10 + 17) on a bubble carried through 97 x 61 x 83 at u = 0.05, 22 us
 // on the 256 x 256 x 128 sessile drop; with one thread per converting cell
 // (each computing the f' of up to 18 new cells from 342 neighbour loads in
 // turn), neighbours tested one by one and the list copied by a launch of its
@@ -138,7 +138,8 @@ __global__ __launch_bounds__(256) void k_conv_mark(const Batch<P> B)
 {
     const Fields<P> &F = B.f[blockIdx.y];
     const int nc = *(volatile const int *)&F.sc->nconv;
-    if (nc != 0) conv_mark(F, nc, blockIdx.x * 4 + (threadIdx.x >> 6), gridDim.x * 4);
+    const int waves = blockDim.x >> 6;
+    if (nc != 0) conv_mark(F, nc, blockIdx.x * waves + (threadIdx.x >> 6), gridDim.x * waves);
 }
 
 // Cell type after rules 1-3 (CLOSE_* codes read as interface) from a cell's
@@ -805,8 +806,9 @@ __global__ __launch_bounds__(LIST_NT) void k_gather_walls(const Batch<P> B, int 
 // Four chunks to a block, and the block that finishes last adds the chunk
 // sums and sets rho_gas(t): no launch of its own. The obstacle fill (blocks
 // before `nw`) reads other cells than it writes and none of the sum's, so the
-// two share a launch. Per launch 10.8 us on the 96^3 bubble between walls
-// (FP64), where fill, chunk sums and final sum took 4.9 + 5.7 + 4.1 in three.
+// two share a launch. Per launch 10.0 us on the 96^3 bubble between walls
+// (FP64), where fill, chunk sums and final sum took 4.9 + 5.7 + 4.1 in three
+// (48^3: 8.0; 9.4 with a barrier at each level of the two trees).
 constexpr int VOL_CHUNKS = 1024;
 constexpr int VOL_NT = 1024;                       // threads per block, 256 to a chunk
 constexpr int VOL_GRID = VOL_CHUNKS / (VOL_NT / 256);
@@ -823,6 +825,13 @@ __global__ __launch_bounds__(VOL_NT) void k_bubble_walls(const Batch<P> B, int n
     if (!prm.bubble) return;
     __shared__ double s[VOL_NT];
     __shared__ int last;
+    // one barrier, then the first wavefront of the values adds them in the
+    // order of a halving tree (w = n / 2, ..., 1: s[t] += s[t + w])
+    auto wave_tree = [](double v) {
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) v += __shfl_down(v, w, 64);
+        return v;
+    };
     const int t = threadIdx.x & 255, c = ((int)blockIdx.x - nw) * (VOL_NT / 256) + (int)(threadIdx.x >> 8);
     const CellRange box = CellRange::from(F.sc->fbox);
     const int n = box.size();
@@ -837,16 +846,16 @@ __global__ __launch_bounds__(VOL_NT) void k_bubble_walls(const Batch<P> B, int n
     }
     s[threadIdx.x] = acc;
     __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if (t < w) s[threadIdx.x] += s[threadIdx.x + w];
-        __syncthreads();
+    if (t < 64) {
+        const double *v = s + threadIdx.x;
+        acc = wave_tree((v[0] + v[128]) + (v[64] + v[192]));
     }
     // the chunk sums go by atomic exchanges, which have taken effect for the
     // whole device when they return: no fence, which would write the L2 back
     // in each of the 256 blocks (12 us)
     auto *part = reinterpret_cast<unsigned long long *>(F.part);
     if (t == 0) {
-        const unsigned long long was = atomicExch(&part[c], (unsigned long long)__double_as_longlong(s[threadIdx.x]));
+        const unsigned long long was = atomicExch(&part[c], (unsigned long long)__double_as_longlong(acc));
         asm volatile("" ::"v"(was));  // waits for the return
     }
     __syncthreads();
@@ -855,12 +864,17 @@ __global__ __launch_bounds__(VOL_NT) void k_bubble_walls(const Batch<P> B, int n
     if (!last) return;
     s[threadIdx.x] = __longlong_as_double((long long)atomicOr(&part[threadIdx.x], 0ull));
     __syncthreads();
-    for (int w = VOL_NT / 2; w > 0; w >>= 1) {
-        if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
-        __syncthreads();
-    }
+    if (threadIdx.x >= 64) return;
+    double e[VOL_NT / 64];
+#pragma unroll
+    for (int k = 0; k < VOL_NT / 64; ++k) e[k] = s[threadIdx.x + 64 * k];
+#pragma unroll
+    for (int h = VOL_NT / 128; h > 0; h >>= 1)
+#pragma unroll
+        for (int k = 0; k < h; ++k) e[k] += e[k + h];
+    const double sum = wave_tree(e[0]);
     if (threadIdx.x == 0) {
-        const double v = prm.n_free - s[0];
+        const double v = prm.n_free - sum;
         if (F.sc->bubble_init) {
             F.sc->gas_v0 = v;
             F.sc->bubble_init = 0;

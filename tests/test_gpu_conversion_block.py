@@ -44,10 +44,12 @@ def body(radius, gas, walls):
     return fill, obst, u
 
 
-# radius 4: about 300 layer cells; 7.4 and 8.4: just below and above 1024
-@pytest.mark.parametrize("radius,below", [(4.0, True), (7.4, True), (8.4, False)])
-@pytest.mark.parametrize("gas,walls,bubble", [(False, False, False), (True, True, True), (True, True, False),
-                                              (True, False, True)])
+# radius 4: about 300 layer cells; 7.4 and 8.4: just below and above 1024; two
+# of radius 27: more than 16384, the bound of the blocks of one wavefront
+@pytest.mark.parametrize("radius,below,gas,walls,bubble", [
+    (r, r < 8, *k) for r in (4.0, 7.4, 8.4)
+    for k in ((False, False, False), (True, True, True), (True, True, False), (True, False, True))
+] + [(27.0, False, False, False, False)])
 def test_small_layers_against_oracle(fslbm, radius, below, gas, walls, bubble):
     fill, obst, u = body(radius, gas, walls)
     model = dict(sigma=1e-3, tau=0.8)
@@ -72,5 +74,7 @@ def test_small_layers_against_oracle(fslbm, radius, below, gas, walls, bubble):
                 assert np.linalg.norm((a - b)[..., fluid]) < 1e-10 * np.linalg.norm(b[..., fluid])
         changed += int((ref[0].flags() != before).sum())
     assert changed > 20
+    if radius > 20:
+        assert sum(g.interface_list().size for g in pair) > 16384
     for g in pair:
         g.close()
