@@ -522,8 +522,9 @@ __global__ __launch_bounds__(256) void k_conv_gather(const Batch<P> B)
 // The whole chain of a small layer in one block per lattice: the phases of
 // the three launches above with barriers between them. A step without
 // conversions is then one launch instead of three (each costs about 3 us on
-// the device whatever it does). The fence drops what the CU's cache
-// holds of the words that the phase before changed by atomics. The host
+// the device whatever it does). Between two phases every wavefront
+// waits until its stores are in the L2, where the atomics act, and then drops
+// what the CU's cache holds of words that the atomics changed. The host
 // takes it for lattices of at most CONV_BLOCK_CELLS interface cells (one
 // thread each): there a few converting cells fit the block's 16 wavefronts.
 // Per pass, FP64: droplet 24^3 (5 steps) 204 -> 180 us; 48^3 bubble between
@@ -539,9 +540,11 @@ __global__ __launch_bounds__(CONV_BLOCK) void k_conv_block(const Batch<P> B)
     const int nc = *(volatile const int *)&F.sc->nconv;
     if (nc != 0) {
         conv_mark(F, nc, threadIdx.x >> 6, CONV_BLOCK / 64);
+        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         conv_close(F, 0, 1);
+        __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
