@@ -443,28 +443,37 @@ __global__ __launch_bounds__(256) void k_adj_stream(const Fields<P> F, const Adj
 }
 
 // The interface box grown by g cells on every side (periodic; an axis that
-// would overlap itself is taken whole). Outside it the adjoints of the FD
-// chain are zero: kbar is not zero only at interface cells, and each stencil,
-// the contact normal's step to its base cell among them, reaches one or two
-// cells further. The buffers start at zero, and the box of a frozen window
-// does not move.
+// would overlap itself is taken whole; g at most an extent). Outside it the
+// adjoints of the FD chain are zero: kbar is not zero only at interface cells,
+// and each stencil, the contact normal's step to its base cell among them,
+// reaches one or two cells further. The buffers start at zero, and the box of
+// a frozen window does not move. Its first cell lies at a negative coordinate
+// where it crosses a low face: at() and contains() wrap.
 struct GrownBox {
     CellRange r;
     int nx, ny, nz;
-    template <class P>
-    __device__ inline GrownBox(const Fields<P> &F, int g) : r(CellRange::from(F.sc->bbox)), nx(F.nx), ny(F.ny), nz(F.nz)
+    __host__ __device__ inline GrownBox(const CellRange &box, int nx_, int ny_, int nz_, int g)
+        : r(box), nx(nx_), ny(ny_), nz(nz_)
     {
         if (r.size() == 0) return;
         grow(r.x0, r.ex, nx, g);
         grow(r.y0, r.ey, ny, g);
         grow(r.z0, r.ez, nz, g);
     }
-    __device__ static inline void grow(int &o, int &e, int n, int g)
+    template <class P>
+    __device__ inline GrownBox(const Fields<P> &F, int g) : GrownBox(CellRange::from(F.sc->bbox), F.nx, F.ny, F.nz, g)
+    {
+    }
+    __host__ __device__ static inline void grow(int &o, int &e, int n, int g)
     {
         o = e + 2 * g < n ? o - g : 0;
-        e = min(e + 2 * g, n);
+        e = e + 2 * g < n ? e + 2 * g : n;
     }
-    __device__ inline Nbr at(int k) const
+    __host__ __device__ inline bool contains(int x, int y, int z) const
+    {
+        return wrapi(x - r.x0, nx) < r.ex && wrapi(y - r.y0, ny) < r.ey && wrapi(z - r.z0, nz) < r.ez;
+    }
+    __host__ __device__ inline Nbr at(int k) const
     {
         const unsigned uk = unsigned(k), row = uk / unsigned(r.ex);
         return Nbr(wrapi(r.x0 + int(uk - row * unsigned(r.ex)), nx), wrapi(r.y0 + int(row % unsigned(r.ey)), ny),
@@ -1409,13 +1418,10 @@ __global__ __launch_bounds__(256) void k_adj_lsqr_phib(const Fields<P> F, const 
 {
     const int n = F.sc->icount, no = F.sc->ocount;
     const GrownBox box(F, 2);  // gb is not zero at interface cells only
-    auto off = [](int v, int o, int n) { return v < o ? v - o + n : v - o; };
     for (int k = blockIdx.x * blockDim.x + threadIdx.x; k < n + no; k += gridDim.x * blockDim.x) {
         const int i = k < n ? interface_list(F)[k] : F.olist[k - n];
         const Nbr nb(i, F.nx, F.ny, F.nz);
-        if (off(nb.x, box.r.x0, F.nx) >= box.r.ex || off(nb.y, box.r.y0, F.ny) >= box.r.ey ||
-            off(nb.z, box.r.z0, F.nz) >= box.r.ez)
-            continue;
+        if (!box.contains(nb.x, nb.y, nb.z)) continue;
         const double v = py_div_t(A.gb, F.N, nb);
         if (k < n) A.phib[i] += v;
         else A.phib[i] = v;

@@ -268,7 +268,7 @@ struct DevScalars {
 // the enumeration follows ascending linear index.
 struct CellRange {
     int x0, y0, z0, ex, ey, ez;
-    __device__ inline int size() const { return ex * ey * ez; }
+    __host__ __device__ inline int size() const { return ex * ey * ez; }
     __device__ inline int cell(int k, int nx, int ny) const
     {
         const int x = k % ex, r = k / ex, y = r % ey, z = r / ey;
@@ -425,14 +425,14 @@ template <class P> struct Batch {
 struct Nbr {
     int ox[3], oy[3], oz[3];
     int x, y, z;
-    __device__ inline Nbr(int i, int nx, int ny, int nz)
+    __host__ __device__ inline Nbr(int i, int nx, int ny, int nz)
     {
         const int yz = i / nx;
         const int zz = yz / ny;
         set(i - yz * nx, yz - zz * ny, zz, nx, ny, nz);
     }
-    __device__ inline Nbr(int x_, int y_, int z_, int nx, int ny, int nz) { set(x_, y_, z_, nx, ny, nz); }
-    __device__ inline void set(int x_, int y_, int z_, int nx, int ny, int nz)
+    __host__ __device__ inline Nbr(int x_, int y_, int z_, int nx, int ny, int nz) { set(x_, y_, z_, nx, ny, nz); }
+    __host__ __device__ inline void set(int x_, int y_, int z_, int nx, int ny, int nz)
     {
         x = x_;
         y = y_;
@@ -446,7 +446,7 @@ struct Nbr {
         oy[0] = y == 0 ? ry + wy : ry - nx; oy[1] = ry; oy[2] = y == ny - 1 ? ry - wy : ry + nx;
         oz[0] = z == 0 ? rz + wz : rz - nxy; oz[1] = rz; oz[2] = z == nz - 1 ? rz - wz : rz + nxy;
     }
-    __device__ inline int at(int dx, int dy, int dz) const
+    __host__ __device__ inline int at(int dx, int dy, int dz) const
     {
         return ox[dx + 1] + oy[dy + 1] + oz[dz + 1];
     }

@@ -189,7 +189,7 @@ struct Tiles {
     }
 };
 
-__device__ inline int wrapi(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
+__host__ __device__ inline int wrapi(int v, int n) { return v < 0 ? v + n : (v >= n ? v - n : v); }
 __device__ inline int gidx(int x, int y, int z, int nx, int ny, int nz)
 {
     return wrapi(x, nx) + nx * (wrapi(y, ny) + ny * wrapi(z, nz));
