@@ -287,6 +287,9 @@ int fslbm_set_interface_fill(fslbm_t h, const double *fill, int in_is_device);
  * opaque device buffer of fslbm_state_bytes() bytes owned by the caller.
  * fslbm_load_state checks that the buffer was saved from a lattice of the
  * same shape, precision and curvature model (FSLBM_E_ARG otherwise).
+ * Every byte of the buffer is written: two saves of one state are equal byte
+ * for byte, and so is a save that follows a load. The distributions of cells
+ * outside the box of all fluid cells, which no step reads, are zeros.
  * Both synchronise the stream. */
 int fslbm_state_bytes(fslbm_t h, size_t *bytes);
 int fslbm_save_state(fslbm_t h, void *dst, size_t bytes);

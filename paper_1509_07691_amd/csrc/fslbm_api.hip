@@ -1400,18 +1400,19 @@ int do_set_interface_fill(fslbm_lattice *h, const double *fill, int is_device)
 
 // Several regions in one launch (a state has 13, and a copy of its own for
 // each of them cost 5 to 8 us whatever its size): 16 bytes per thread and
-// step, 16-byte aligned at both ends.
+// step, 16-byte aligned at both ends; zeros from `bytes` to `room`.
 struct CopySet {
     static constexpr int MAX = 16;
     const char *src[MAX];
     char *dst[MAX];
-    size_t bytes[MAX];
+    size_t bytes[MAX], room[MAX];
     int n = 0;
-    void add(const void *s, void *d, size_t b)
+    void add(const void *s, void *d, size_t b, size_t r = 0)
     {
         src[n] = (const char *)s;
         dst[n] = (char *)d;
-        bytes[n++] = b;
+        bytes[n] = b;
+        room[n++] = std::max(b, r);
     }
 };
 __global__ __launch_bounds__(256) void k_copy_set(const CopySet c)
@@ -1420,7 +1421,7 @@ __global__ __launch_bounds__(256) void k_copy_set(const CopySet c)
     for (int r = 0; r < c.n; ++r) {
         const size_t words = c.bytes[r] / 16;
         for (size_t i = t; i < words; i += stride) ((uint4 *)c.dst[r])[i] = ((const uint4 *)c.src[r])[i];
-        for (size_t i = 16 * words + t; i < c.bytes[r]; i += stride) c.dst[r][i] = c.src[r][i];
+        for (size_t i = 16 * words + t; i < c.room[r]; i += stride) c.dst[r][i] = i < c.bytes[r] ? c.src[r][i] : 0;
     }
 }
 int enqueue_copies(const CopySet &c, hipStream_t st)
@@ -1466,6 +1467,40 @@ int enqueue_copy_box(const fslbm_lattice *h, const void *src, void *dst, const D
     return 0;
 }
 
+// The distributions of a saved state: those of the cells in the fluid box,
+// zeros elsewhere (and between the planes), so that every byte of a saved
+// state follows from the lattice's. dst = src clears in place what lies
+// outside the box.
+template <class S>
+__global__ __launch_bounds__(256) void k_save_box(const S *src, S *dst, const DevScalars *sc, int nx, int ny, int NS)
+{
+    const CellRange box = CellRange::from(sc->fbox);
+    for (long long k = blockIdx.x * 256LL + threadIdx.x; k < NS; k += gridDim.x * 256LL) {
+        const int i = int(k), yz = i / nx, x = i - yz * nx, z = yz / ny, y = yz - z * ny;
+        const bool in = x >= box.x0 && x < box.x0 + box.ex && y >= box.y0 && y < box.y0 + box.ey && z >= box.z0 &&
+                        z < box.z0 + box.ez;
+        if (in && dst == src) continue;
+        S v[NQ];
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) v[q] = in ? src[(size_t)q * NS + i] : S(0);
+#pragma unroll
+        for (int q = 0; q < NQ; ++q) dst[(size_t)q * NS + i] = v[q];
+    }
+}
+int enqueue_save_box(const fslbm_lattice *h, const void *src, void *dst)
+{
+    const DevScalars *sc = (const DevScalars *)(h->ws + h->L.sc);
+    const int g = std::min(16384, cell_blocks(h->NS));
+    switch (fbytes(h->prec)) {
+    case 8: k_save_box<double><<<g, 256, 0, h->stream>>>((const double *)src, (double *)dst, sc, h->nx, h->ny, h->NS); break;
+    case 4: k_save_box<float><<<g, 256, 0, h->stream>>>((const float *)src, (float *)dst, sc, h->nx, h->ny, h->NS); break;
+    default:
+        k_save_box<uint16_t><<<g, 256, 0, h->stream>>>((const uint16_t *)src, (uint16_t *)dst, sc, h->nx, h->ny, h->NS);
+    }
+    HIP_OK(hipGetLastError());
+    return 0;
+}
+
 // Parts of the workspace that make up the state (offset, bytes); the first
 // entry is the current distribution buffer.
 std::vector<std::pair<size_t, size_t>> state_regions(const fslbm_lattice *h)
@@ -1505,6 +1540,7 @@ size_t state_bytes(const fslbm_lattice *h)
 // The regions between the workspace and a state buffer: to `dst`, or from
 // `src`. The distributions go by the fluid box of the side that is read, the
 // rest in one launch; a buffer that is not 16-byte aligned takes plain copies.
+// A saved buffer is written whole, its padding included.
 int copy_state(fslbm_lattice *h, char *dst, const char *src)
 {
     const auto regions = state_regions(h);
@@ -1516,21 +1552,29 @@ int copy_state(fslbm_lattice *h, char *dst, const char *src)
         off += align256(r.second);
     }
     off = 256;
-    for (size_t k = 0; k < regions.size(); ++k) {
+    int rc = 0;
+    for (size_t k = 0; k < regions.size() && !rc; ++k) {
         const auto &r = regions[k];
         const char *from = dst ? h->ws + r.first : src + off;
         char *to = dst ? dst + off : h->ws + r.first;
+        const size_t room = align256(r.second);
         if (!aligned) {
+            if (dst && k == 0) rc = enqueue_save_box(h, from, h->ws + r.first);
             HIP_OK(hipMemcpyAsync(to, from, r.second, hipMemcpyDeviceToDevice, h->stream));
+            if (dst && room > r.second) HIP_OK(hipMemsetAsync(to + r.second, 0, room - r.second, h->stream));
         } else if (k == 0) {
-            const int rc = enqueue_copy_box(h, from, to, (const DevScalars *)(dst ? h->ws + h->L.sc : src + sc_off));
-            if (rc) return rc;
+            if (dst) {
+                rc = enqueue_save_box(h, from, to);
+                c.add(from, to + r.second, 0, room - r.second);
+            } else {
+                rc = enqueue_copy_box(h, from, to, (const DevScalars *)(src + sc_off));
+            }
         } else {
-            c.add(from, to, r.second);
+            c.add(from, to, r.second, dst ? room : 0);
         }
-        off += align256(r.second);
+        off += room;
     }
-    return aligned ? enqueue_copies(c, h->stream) : 0;
+    return aligned && !rc ? enqueue_copies(c, h->stream) : rc;
 }
 
 // ------------------------------------------------ frozen-topology window
@@ -2635,9 +2679,11 @@ int fslbm_save_state(fslbm_t h, void *dst, size_t bytes)
     if (bytes < state_bytes(h)) return fail(FSLBM_E_SHAPE, "state buffer has %zu bytes, %zu needed", bytes, state_bytes(h));
     const int lrc = dispatch<OpListHome>(h);
     if (lrc) return lrc;
-    StateHeader hd{STATE_MAGIC, h->nx, h->ny, h->nz, h->prec, h->curv, 0, h->steps};
+    const StateHeader hd{STATE_MAGIC, h->nx, h->ny, h->nz, h->prec, h->curv, 0, h->steps};
+    char head[256] = {};
+    memcpy(head, &hd, sizeof hd);
     char *d = (char *)dst;
-    HIP_OK(hipMemcpyAsync(d, &hd, sizeof hd, hipMemcpyHostToDevice, h->stream));
+    HIP_OK(hipMemcpyAsync(d, head, sizeof head, hipMemcpyHostToDevice, h->stream));
     const int rc = copy_state(h, d, nullptr);
     if (rc) return rc;
     HIP_OK(hipStreamSynchronize(h->stream));
