@@ -1537,14 +1537,29 @@ size_t state_bytes(const fslbm_lattice *h)
     return b;
 }
 
+// Memory of the lattice's own device: what its kernels may address. Another
+// device's needs peer access, and the host's is slow to reach.
+bool own_memory(const fslbm_lattice *h, const void *p)
+{
+    hipPointerAttribute_t attr;
+    if (hipPointerGetAttributes(&attr, p) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    return attr.type == hipMemoryTypeDevice && attr.device == h->device;
+}
+
 // The regions between the workspace and a state buffer: to `dst`, or from
 // `src`. The distributions go by the fluid box of the side that is read, the
-// rest in one launch; a buffer that is not 16-byte aligned takes plain copies.
-// A saved buffer is written whole, its padding included.
+// rest in one launch; a buffer that is not 16-byte aligned or not in the
+// lattice's own device memory takes plain copies. A saved buffer is written
+// whole, its padding included.
 int copy_state(fslbm_lattice *h, char *dst, const char *src)
 {
+    static const char zeros[256] = {};
     const auto regions = state_regions(h);
-    const bool aligned = (reinterpret_cast<uintptr_t>(dst ? dst : src) & 15) == 0;
+    const char *buf = dst ? dst : src;
+    const bool kernels = (reinterpret_cast<uintptr_t>(buf) & 15) == 0 && own_memory(h, buf);
     CopySet c;
     size_t off = 256, sc_off = 0;
     for (auto &r : regions) {
@@ -1558,10 +1573,11 @@ int copy_state(fslbm_lattice *h, char *dst, const char *src)
         const char *from = dst ? h->ws + r.first : src + off;
         char *to = dst ? dst + off : h->ws + r.first;
         const size_t room = align256(r.second);
-        if (!aligned) {
+        if (!kernels) {
             if (dst && k == 0) rc = enqueue_save_box(h, from, h->ws + r.first);
             HIP_OK(hipMemcpyAsync(to, from, r.second, hipMemcpyDeviceToDevice, h->stream));
-            if (dst && room > r.second) HIP_OK(hipMemsetAsync(to + r.second, 0, room - r.second, h->stream));
+            if (dst && room > r.second)
+                HIP_OK(hipMemcpyAsync(to + r.second, zeros, room - r.second, hipMemcpyHostToDevice, h->stream));
         } else if (k == 0) {
             if (dst) {
                 rc = enqueue_save_box(h, from, to);
@@ -1574,7 +1590,7 @@ int copy_state(fslbm_lattice *h, char *dst, const char *src)
         }
         off += room;
     }
-    return aligned && !rc ? enqueue_copies(c, h->stream) : rc;
+    return kernels && !rc ? enqueue_copies(c, h->stream) : rc;
 }
 
 // ------------------------------------------------ frozen-topology window

@@ -89,3 +89,27 @@ def test_buffer_alignment(fs, precision, model, offset):
         for k in want:
             assert np.array_equal(got[k], want[k]), k
     lat.close()
+
+
+@pytest.mark.parametrize("precision,model", FORMS)
+def test_buffer_in_pinned_host_memory(fs, precision, model):
+    """A buffer outside the lattice's device memory (pinned host memory here,
+    another device's elsewhere) goes by copies of the runtime: the same
+    bytes, and a load from it continues the run."""
+    import torch
+
+    lat = make(fs, precision, model)
+    lat.step(10)
+    ref = save(fs, lat, 0xA5).cpu().numpy()
+    buf = torch.empty(ref.size, dtype=torch.uint8, pin_memory=True)
+    buf.fill_(0x5A)
+    fs.fslbm_save_state(lat.handle, buf.data_ptr(), ref.size)
+    assert np.array_equal(buf.numpy(), ref)
+    lat.step(15)
+    want = fields(lat)
+    fs.fslbm_load_state(lat.handle, buf.data_ptr(), ref.size)
+    lat.step(15)
+    got = fields(lat)
+    for k in want:
+        assert np.array_equal(got[k], want[k]), k
+    lat.close()
