@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 #include <new>
 #include <string>
@@ -205,7 +206,7 @@ struct fslbm_lattice {
     unsigned version;  // bumped whenever launch arguments change
     unsigned long long epoch;  // bumped whenever the state changes other than by stepping
     int frozen;        // 1 inside a frozen-topology window
-    int icount0;       // interface cells at creation (sizes the list-kernel grids)
+    int icount0;       // interface cells that size the list kernels' grids and choose their forms (size_lists)
     int ocount0;       // obstacle cells next to the fluid (sizes the reflection grid)
     int bubble;        // bubble model on (FSLBM_OPT_BUBBLE)
     double n_free;     // non-obstacle cells
@@ -931,8 +932,8 @@ Batch<P> make_batch(const fslbm_batch *b, int &maxN, bool &any_srt, bool &any_tr
 inline hipStream_t bstream(const fslbm_batch *b) { return b->hs[0]->stream; }
 
 // Grid of the interface-list kernels of a batch: about one thread per
-// interface cell at creation (the loops are grid-stride, so later growth is
-// still covered), at least 8 and at most 512 blocks of 256 threads (their
+// interface cell when last sized (the loops are grid-stride, so growth since
+// then is still covered), at least 8 and at most 512 blocks of 256 threads (their
 // like in blocks of nt) per lattice.
 inline int batch_list_blocks(const fslbm_batch *b, int cells_per_block, int nt = 256)
 {
@@ -962,7 +963,7 @@ int enqueue_geometry(const fslbm_batch *b, const Batch<P> &A, int maxN, int eos 
     const hipStream_t st = bstream(b);
     const dim3 tg(std::min(GEOM_GRID, std::max(1, maxN / 512)), n);
     bool any_fd = false, any_fd_wall = false, any_lsqr = false, any_tr = false, stored = true;
-    long long fd_cells = 0;  // interface cells (at creation) of the FD lattices
+    long long fd_cells = 0;  // interface cells of the FD lattices when last sized
     for (auto *h : b->hs) {
         if (h->curv == FSLBM_CURV_LSQR) stored &= keeps_contact(h);
         if (h->curv == FSLBM_CURV_FD) fd_cells += h->icount0;
@@ -1064,7 +1065,7 @@ int enqueue_step_kernels(fslbm_batch *b, const void *fsrc = nullptr, void *fdst 
     // without walls); it shares a launch with phi = m / rho in a frozen step,
     // else with the bubble's volume sum where there is one
     int maxo = 0, maxi = 0;
-    long long layer = 0;  // interface cells (at creation) of the batch
+    long long layer = 0;  // interface cells of the batch when last sized
     bool any_bubble = false;
     for (auto *h : b->hs) {
         maxo = std::max(maxo, h->ocount0);
@@ -1656,6 +1657,19 @@ Adj adj_fields(const AdjWindow &w, const fslbm_lattice *h, int par)
     return A;
 }
 
+// Sizes the list kernels by `count` interface cells once it is a quarter off
+// the number that sized them last: a layer grows or shrinks as a body moves,
+// breaks up or is loaded, and the forms for small layers are slow on large
+// ones (the conversion chain of 24,000 cells takes 864 us a step in one block
+// and 49 in the launches for that size), while a changed size costs the
+// capture of a new graph, so it does not follow every count.
+void size_lists(fslbm_lattice *h, int count)
+{
+    if (std::abs(count - h->icount0) <= h->icount0 / 4) return;
+    h->icount0 = count;
+    h->version += 1;
+}
+
 // Reads the fluid box back (synchronises the stream) and sizes the bulk
 // stream-collide grid to it; a changed grid invalidates captured graphs.
 int refresh_box(fslbm_lattice *h)
@@ -1671,6 +1685,7 @@ int refresh_box(fslbm_lattice *h)
     const int blocks = xcd_grid((cells + SC_BLOCK - 1) / SC_BLOCK);
     h->boundary_cells = (long long)sc.icount + sc.wcount;
     h->box_cells = cells;
+    size_lists(h, sc.icount);
     if (sc.wcount != h->wcount) {
         h->wcount = sc.wcount;
         h->version += 1;
@@ -2727,10 +2742,11 @@ int fslbm_load_state(fslbm_t h, const void *src, size_t bytes)
     enqueue_wall_index(h);  // the state brings its own wall list
     HIP_OK(hipGetLastError());
     HIP_OK(hipStreamSynchronize(h->stream));
-    // the loaded state brings its own obstacle list (launch sizing only)
+    // the loaded state brings its own lists (launch sizing only)
     int ic = 0, oc = 0;
     const int rc = read_counts(h, ic, oc);
     if (rc) return rc;
+    h->icount0 = ic;
     h->ocount0 = oc;
     return refresh_box(h);
 }

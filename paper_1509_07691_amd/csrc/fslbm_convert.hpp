@@ -526,7 +526,8 @@ __global__ __launch_bounds__(256) void k_conv_gather(const Batch<P> B)
 // waits until its stores are in the L2, where the atomics act, and then drops
 // what the CU's cache holds of words that the atomics changed. The host
 // takes it for lattices of at most CONV_BLOCK_CELLS interface cells (one
-// thread each): there a few converting cells fit the block's 16 wavefronts.
+// thread each) when they were last sized: there a few converting cells fit the
+// block's 16 wavefronts. A layer that has grown since is walked in rounds.
 // Per pass, FP64: droplet 24^3 (5 steps) 204 -> 180 us; 48^3 bubble between
 // walls (20 steps, with the launch that the walls share with the volume sum)
 // 1157 -> 925 us.
