@@ -777,9 +777,9 @@ def run_workload(dev, stream, name, prec, steps, warmup, split=None, graph=False
            "split_passes": split,
            "stream_collide_us": round(1e3 * sc_ms / steps, 3), "algorithmic_bytes_per_launch": int(launch),
            "stream_collide_GBs": round(achieved, 1), "roofline_frac": round(achieved / HBM_PEAK_GBS, 4),
-           "phases_ms_per_step": {k: round(v / steps, 4) for k, v in
-                                  zip(("stream_collide", "stream_collide_interface_list", "conversion",
-                                       "list_update", "obstacle_fill_and_curvature"), phase)}}
+           "phases_ms_per_step": {k: round(phase[i] / steps, 4) for i, k in
+                                  ((0, "stream_collide"), (1, "stream_collide_interface_list"),
+                                   (2, "conversion_and_list_update"), (4, "obstacle_fill_and_curvature"))}}
     if graph:
         batch.set_graph(True)
         batch.step(2)

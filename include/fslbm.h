@@ -269,8 +269,9 @@ void fslbm_batch_destroy(fslbm_batch_t b);
  * FSLBM_OPT_TIMING is on, phase_ms[5]: [0] stream-collide of liquid cells,
  * [1] stream-collide with mass exchange of interface cells, [2] cell
  * conversion and the update of the interface list, [3] nothing (the list
- * update was a launch of its own), [4] obstacle fill and curvature; *steps
- * receives the number of timed steps. Synchronises. */
+ * update was a launch of its own), [4] obstacle fill, bubble volume and
+ * curvature (a step with frozen cell types fills the obstacle cells in [2]);
+ * *steps receives the number of timed steps. Synchronises. */
 int fslbm_read_timing(fslbm_t h, double *phase_ms, int64_t *steps);
 int fslbm_reset_timing(fslbm_t h);
 

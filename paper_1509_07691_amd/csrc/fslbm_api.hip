@@ -170,8 +170,8 @@ struct fslbm_batch {
     std::vector<fslbm_lattice *> hs;
     std::vector<unsigned> versions;  // handle versions the graphs were captured at
     int prec;
-    // optional phase timing: events around stream-collide, conversion,
-    // compaction and obstacle fill + curvature of every step
+    // optional phase timing: events around stream-collide, conversion and
+    // obstacle fill + curvature of every step
     int timing;
     std::vector<hipEvent_t> ev;
     int ev_used;  // steps recorded in ev since the last fold
@@ -943,13 +943,13 @@ inline int batch_list_blocks(const fslbm_batch *b, int cells_per_block, int nt =
 }
 
 template <class P>
-int enqueue_compaction(const fslbm_batch *b, const Batch<P> &A, int maxN, int which, int force)
+int enqueue_compaction(const fslbm_batch *b, const Batch<P> &A, int maxN, int which)
 {
     const unsigned n = (unsigned)b->hs.size();
     const hipStream_t st = bstream(b);
-    k_compact_count<P><<<dim3(cmp_blocks(maxN), n), 256, 0, st>>>(A, which, force);
-    k_compact_scan<P><<<dim3(1, n), 1024, 0, st>>>(A, which, force, cmp_blocks(maxN));
-    k_compact_write<P><<<dim3(cmp_blocks(maxN), n), 256, 0, st>>>(A, which, force);
+    k_compact_count<P><<<dim3(cmp_blocks(maxN), n), 256, 0, st>>>(A, which);
+    k_compact_scan<P><<<dim3(1, n), 1024, 0, st>>>(A, which, cmp_blocks(maxN));
+    k_compact_write<P><<<dim3(cmp_blocks(maxN), n), 256, 0, st>>>(A, which);
     HIP_OK(hipGetLastError());
     return 0;
 }
@@ -1253,12 +1253,12 @@ int enqueue_init(fslbm_lattice *h, const double *fill, const uint8_t *obstacle)
     int maxN;
     bool s_, t_;
     const Batch<P> A = make_batch<P>(&h->self, maxN, s_, t_);
-    int rc = enqueue_compaction<P>(&h->self, A, maxN, 1, 1);
-    if (!rc) rc = enqueue_compaction<P>(&h->self, A, maxN, 2, 1);
+    int rc = enqueue_compaction<P>(&h->self, A, maxN, 1);
+    if (!rc) rc = enqueue_compaction<P>(&h->self, A, maxN, 2);
     if (rc) return rc;
     enqueue_wall_index(h);
     k_fill_bytes<<<std::min(4096, cell_blocks(N)), 256, 0, h->stream>>>(F.conv, N, 0);
-    rc = enqueue_compaction<P>(&h->self, A, maxN, 0, 1);
+    rc = enqueue_compaction<P>(&h->self, A, maxN, 0);
     if (rc) return rc;
     k_obstacle_fill<P><<<dim3(list_blocks(N), 1), 256, 0, h->stream>>>(A);
     HIP_OK(hipGetLastError());

@@ -619,10 +619,9 @@ __device__ inline void tile_range(int N, int &t0, int &t1)
 }
 
 template <class P>
-__global__ __launch_bounds__(256) void k_compact_count(const Batch<P> B, int which, int force)
+__global__ __launch_bounds__(256) void k_compact_count(const Batch<P> B, int which)
 {
     const Fields<P> &F = B.f[blockIdx.y];
-    if (!force && F.sc->nconv == 0) return;
     const uint8_t *src; uint8_t want; int32_t *list; int *count; CellRange range;
     compact_source(F, which, src, want, list, count, range);
     __shared__ int lw[4];
@@ -643,10 +642,9 @@ __global__ __launch_bounds__(256) void k_compact_count(const Batch<P> B, int whi
 // One block per lattice: exclusive scan of the block counts, list length;
 // the interface bounding box is reset for the write pass.
 template <class P>
-__global__ __launch_bounds__(1024) void k_compact_scan(const Batch<P> B, int which, int force, int nblocks)
+__global__ __launch_bounds__(1024) void k_compact_scan(const Batch<P> B, int which, int nblocks)
 {
     const Fields<P> &F = B.f[blockIdx.y];
-    if (!force && F.sc->nconv == 0) return;
     const uint8_t *src; uint8_t want; int32_t *list; int *count; CellRange range;
     compact_source(F, which, src, want, list, count, range);
     __shared__ int lw[16];
@@ -670,10 +668,9 @@ __global__ __launch_bounds__(1024) void k_compact_scan(const Batch<P> B, int whi
 }
 
 template <class P>
-__global__ __launch_bounds__(256) void k_compact_write(const Batch<P> B, int which, int force)
+__global__ __launch_bounds__(256) void k_compact_write(const Batch<P> B, int which)
 {
     const Fields<P> &F = B.f[blockIdx.y];
-    if (!force && F.sc->nconv == 0) return;
     const uint8_t *src; uint8_t want; int32_t *list; int *count; CellRange range;
     compact_source(F, which, src, want, list, count, range);
     __shared__ int lw[4];

@@ -387,7 +387,7 @@ template <class P> struct Fields {
     S *fdst;           // f'(t+1)
     uint8_t *flags;
     uint8_t *conv;
-    uint8_t *near;  // low byte of the step number when within 2 cells of a filling or emptying cell
+    uint8_t *near;  // low byte of the step number in the 7 x 7 x 7 box around a filling or emptying cell
     uint32_t *mark;
     R *m, *rho, *phi, *K, *nrm, *plic;
     R *cnrm;           // FD wetting: contact normal of obstacle cells (3 planes, 0 = none)

@@ -265,7 +265,7 @@ def fslbm_steps_taken(h):
 
 def fslbm_read_timing(h):
     """(phase milliseconds [liquid stream-collide, interface stream-collide,
-    conversion, compaction, geometry], steps)."""
+    conversion and list update, nothing, geometry], steps)."""
     out = np.zeros(5)
     steps = ctypes.c_int64(0)
     _check(load_library().fslbm_read_timing(h, _dptr(out), ctypes.byref(steps)))
